@@ -102,10 +102,22 @@ constexpr int bitrev(int i, int bits) {
   return r;
 }
 
-// In-register radix-R DFT (R = 1, 2, 4, 8, 16): radix-2 decimation in
-// frequency, then a compile-time bit-reversal rename.
+// A pass multiplies its radix-R inputs by powers of a twiddle and transforms
+// them, in one of two forms.  Folded: the twiddles go into a decimation-in-time
+// DFT's butterflies, six fused multiply-adds each; with R = 16 a pass takes 236
+// operations, the twiddles' formation included, the separate form (R - 1
+// products, then the DFT) 321 and more registers.  FP64 takes the folded form
+// (4096^2 step 840 -> 825 us).  FP32 keeps the separate one: a transform's
+// result shrinks by the rounding of the low-order roots, which a run adds up
+// step after step, and the folded form shrinks more for R <= 8 (512 points:
+// 2.9e-8 per transform against 2.4e-8).
+template <typename T, int R>
+constexpr bool kFolded = sizeof(T) == 8;
+
+// Separate form: radix-2 decimation in frequency, then a compile-time
+// bit-reversal rename.
 template <typename T, int DIR, int R>
-__device__ __forceinline__ void dft_reg(c2<T>* v) {
+__device__ __forceinline__ void dft_dif(c2<T>* v) {
   if constexpr (R >= 2) {
 #pragma unroll
     for (int span = R / 2; span >= 1; span >>= 1) {
@@ -129,6 +141,176 @@ __device__ __forceinline__ void dft_reg(c2<T>* v) {
   }
 }
 
+// cos(k pi / 8), k = 0 .. 3 (sin(k pi / 8) is the mirrored entry), to double
+// precision.
+__device__ constexpr double kCosPi8[5] = {1.0, 0.92387953251128675613, 0.70710678118654752440,
+                                          0.38268343236508977173, 0.0};
+
+// Butterfly a, b <- a + c b, a - c b with c = w, or (TURN) w turned by a
+// quarter: w exp(DIR i pi / 2).  DIR > 0 takes conj(w).  Six fused
+// multiply-adds: the sum by two per component, the difference as 2a minus it.
+template <typename T, int DIR, bool TURN>
+__device__ __forceinline__ void bfly(c2<T>& a, c2<T>& b, c2<T> w) {
+  const T wy = DIR < 0 ? w.y : -w.y;
+  T x, y;
+  if constexpr (!TURN) {
+    x = fma(-wy, b.y, fma(w.x, b.x, a.x));
+    y = fma(wy, b.x, fma(w.x, b.y, a.y));
+  } else if constexpr (DIR < 0) {  // -i w b
+    x = fma(wy, b.x, fma(w.x, b.y, a.x));
+    y = fma(wy, b.y, fma(-w.x, b.x, a.y));
+  } else {  // +i conj(w) b
+    x = fma(-wy, b.x, fma(-w.x, b.y, a.x));
+    y = fma(-wy, b.y, fma(w.x, b.x, a.y));
+  }
+  b = {fma(T(2), a.x, -x), fma(T(2), a.y, -y)};
+  a = {x, y};
+}
+// The same with c = 1, or (TURN) exp(DIR i pi / 2).
+template <typename T, int DIR, bool TURN>
+__device__ __forceinline__ void bfly1(c2<T>& a, c2<T>& b) {
+  const c2<T> t = !TURN ? b : (DIR < 0 ? c2<T>{b.y, -b.x} : c2<T>{-b.y, b.x});
+  b = csub(a, t);
+  a = cadd(a, t);
+}
+
+// The twiddles of a radix-R pass: v[r] is multiplied by w^r before the
+// length-R DFT.  Folded into the DFT's butterflies (decimation in time), level
+// S = 2, 4, .. R needs w^(R/S) exp(-2 pi i k / S), k < S/4 (k = 0 for S = 2),
+// the others being quarter turns of these: R/2 values instead of R - 1
+// powers, formed from w in FP64 (product depth <= 4, error ~1e-15) and rounded
+// once to T.
+template <typename T, int R, bool FOLDED = kFolded<T, R>>
+struct PassW {
+  static constexpr int N = R >= 4 ? R / 2 : 1;
+  c2<T> w[N];  // level R: w[0 .. R/4), level R/2: the next R/8, .., 4: 1, 2: 1
+  __device__ __forceinline__ void set(c2<double> w1) {
+    c2<double> b = w1;  // w^(R/S)
+#pragma unroll
+    for (int S = R; S >= 2; S >>= 1) {
+      const int n = S >= 4 ? S / 4 : 1, o = off(S);
+#pragma unroll
+      for (int k = 0; k < n; ++k) {
+        // exp(-2 pi i k / S) = cos, -sin of (16 k / S) pi / 8
+        const int q = 16 * k / S;
+        const c2<double> z = k == 0 ? b : cmul(b, c2<double>{kCosPi8[q], -kCosPi8[4 - q]});
+        w[o + k] = {static_cast<T>(z.x), static_cast<T>(z.y)};
+      }
+      b = cmul(b, b);
+    }
+  }
+  static constexpr int off(int S) {
+    int o = 0;
+    for (int s = R; s > S; s >>= 1) o += s >= 4 ? s / 4 : 1;
+    return o;
+  }
+};
+// Separate form: the powers w^r (r = 1 .. R-1) from a product tree of depth <= 3
+// in FP64 (error ~1e-15), each rounded once.
+template <typename T, int R>
+struct PassW<T, R, false> {
+  c2<T> w[R];
+  __device__ __forceinline__ void put(int r, c2<double> a) {
+    w[r] = {static_cast<T>(a.x), static_cast<T>(a.y)};
+  }
+  __device__ __forceinline__ void set(c2<double> w1) {
+    if constexpr (R >= 2) put(1, w1);
+    if constexpr (R >= 4) {
+      const c2<double> w2 = cmul(w1, w1), w3 = cmul(w2, w1);
+      put(2, w2);
+      put(3, w3);
+      if constexpr (R >= 8) {
+        const c2<double> w4 = cmul(w2, w2);
+        const c2<double> hi[4] = {w4, cmul(w4, w1), cmul(w4, w2), cmul(w4, w3)};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) put(4 + r, hi[r]);
+        if constexpr (R >= 16) {
+          const c2<double> w8 = cmul(w4, w4);
+          put(8, w8);
+          put(9, cmul(w8, w1));
+          put(10, cmul(w8, w2));
+          put(11, cmul(w8, w3));
+#pragma unroll
+          for (int r = 0; r < 4; ++r) put(12 + r, cmul(w8, hi[r]));
+        }
+      }
+    }
+  }
+};
+
+// Radix-R DFT of v (R = 1, 2, 4, 8, 16; natural order in and out) with the
+// pass's twiddles: v[k] <- sum_r w^r v[r] exp(DIR 2 pi i r k / R), w conjugated
+// for DIR > 0.
+template <typename T, int DIR, int R, bool FOLDED>
+__device__ __forceinline__ void dft_tw(c2<T>* v, const PassW<T, R, FOLDED>& pw) {
+  if constexpr (!FOLDED) {
+#pragma unroll
+    for (int r = 1; r < R; ++r) v[r] = DIR < 0 ? cmul(v[r], pw.w[r]) : cmulc(v[r], pw.w[r]);
+    dft_dif<T, DIR, R>(v);
+  } else {
+    constexpr int bits = ilog2(R);
+    c2<T> a[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) a[i] = v[bitrev(i, bits)];
+#pragma unroll
+    for (int S = 2; S <= R; S <<= 1) {
+#pragma unroll
+      for (int g = 0; g < R; g += S) {
+#pragma unroll
+        for (int k = 0; k < S / 2; ++k) {
+          c2<T>& x = a[g + k];
+          c2<T>& y = a[g + k + S / 2];
+          const int n = S >= 4 ? S / 4 : 1;
+          if (k < n)
+            bfly<T, DIR, false>(x, y, pw.w[PassW<T, R, FOLDED>::off(S) + k]);
+          else
+            bfly<T, DIR, true>(x, y, pw.w[PassW<T, R, FOLDED>::off(S) + k - n]);
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = a[i];
+  }
+}
+
+// The same without twiddles.
+template <typename T, int DIR, int R, bool FOLDED = kFolded<T, R>>
+__device__ __forceinline__ void dft_reg(c2<T>* v) {
+  if constexpr (!FOLDED) {
+    dft_dif<T, DIR, R>(v);
+  } else if constexpr (R >= 2) {
+    constexpr int bits = ilog2(R);
+    c2<T> a[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) a[i] = v[bitrev(i, bits)];
+#pragma unroll
+    for (int S = 2; S <= R; S <<= 1) {
+#pragma unroll
+      for (int g = 0; g < R; g += S) {
+#pragma unroll
+        for (int k = 0; k < S / 2; ++k) {
+          c2<T>& x = a[g + k];
+          c2<T>& y = a[g + k + S / 2];
+          if (k == 0)
+            bfly1<T, DIR, false>(x, y);
+          else if (4 * k == S)
+            bfly1<T, DIR, true>(x, y);
+          else {
+            const int q = (16 * k / S) & 3;  // angle within the quarter
+            const c2<T> w = {static_cast<T>(kCosPi8[q]), static_cast<T>(-kCosPi8[4 - q])};
+            if (4 * k < S)
+              bfly<T, DIR, false>(x, y, w);
+            else
+              bfly<T, DIR, true>(x, y, w);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = a[i];
+  }
+}
+
 // Radix of the first Stockham pass: L / E^n with 1 < R0 <= E.
 constexpr int first_radix(int L, int E) {
   int r = L;
@@ -144,44 +326,6 @@ constexpr int fft_passes(int L, int E) {
   int n = 0;
   for (int Ns = first_radix(L, E); Ns < L; Ns *= E) ++n;
   return n;
-}
-
-// v[r] *= w^r (r = 1 .. E-1; conj(w)^r for DIR > 0).  The powers come from
-// a product tree of depth <= 3 in FP64 (error ~1e-15), each rounded once to T.
-// With v1 != nullptr (TWO) the same powers also multiply v1.
-template <typename T, int DIR, int E, bool TWO = false>
-__device__ __forceinline__ void twiddle_powers(c2<T>* v, c2<double> w1, c2<T>* v1 = nullptr) {
-  auto app = [&](int r, c2<double> wd) {
-    const c2<T> w = {static_cast<T>(wd.x), static_cast<T>(wd.y)};
-    v[r] = DIR < 0 ? cmul(v[r], w) : cmulc(v[r], w);
-    if constexpr (TWO) v1[r] = DIR < 0 ? cmul(v1[r], w) : cmulc(v1[r], w);
-  };
-  if constexpr (E >= 2) app(1, w1);
-  if constexpr (E >= 4) {
-    const c2<double> w2 = cmul(w1, w1);
-    app(2, w2);
-    app(3, cmul(w2, w1));
-    if constexpr (E >= 8) {
-      const c2<double> w4 = cmul(w2, w2);
-      app(4, w4);
-      app(5, cmul(w4, w1));
-      app(6, cmul(w4, w2));
-      app(7, cmul(w4, cmul(w2, w1)));
-      if constexpr (E >= 16) {
-        const c2<double> w8 = cmul(w4, w4);
-        app(8, w8);
-#pragma unroll
-        for (int r = 9; r < 16; ++r) {
-          // w^r = w^8 w^(r-8), r - 8 in 1 .. 7
-          const int a = r - 8;
-          c2<double> wa = (a & 4) ? w4 : c2<double>{1.0, 0.0};
-          if (a & 2) wa = (a & 4) ? cmul(wa, w2) : w2;
-          if (a & 1) wa = (a & 6) ? cmul(wa, w1) : w1;
-          app(r, cmul(w8, wa));
-        }
-      }
-    }
-  }
 }
 
 // LDS slot of element i of a transform's exchange area, a permutation within
@@ -260,8 +404,9 @@ __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < E; ++r) v[r] = lds[lds_slot<T>(t + r * P) * LS];
-      twiddle_powers<T, DIR, E>(v, w);
-      dft_reg<T, DIR, E>(v);
+      PassW<T, E> pw;
+      pw.set(w);
+      dft_tw<T, DIR, E>(v, pw);
       if (pass + 1 == NP) break;
       __syncthreads();
       const int k = t & (Ns - 1);
@@ -324,9 +469,10 @@ __device__ __forceinline__ void fft_group2(c2<T>* v0, c2<T>* v1, c2<T>* lds0, c2
         v0[r] = lds0[lds_slot<T>(t + r * P) * LS];
         v1[r] = lds1[lds_slot<T>(t + r * P) * LS];
       }
-      twiddle_powers<T, DIR, E, true>(v0, w, v1);
-      dft_reg<T, DIR, E>(v0);
-      dft_reg<T, DIR, E>(v1);
+      PassW<T, E> pw;
+      pw.set(w);
+      dft_tw<T, DIR, E>(v0, pw);
+      dft_tw<T, DIR, E>(v1, pw);
       if (pass + 1 == NP) break;
       __syncthreads();
       const int k = t & (Ns - 1);
@@ -345,18 +491,19 @@ __device__ __forceinline__ void fft_group2(c2<T>* v0, c2<T>* v1, c2<T>* lds0, c2
 // multiples of pi/16, correctly rounded).  The table entry m = t + q L/E of
 // exp(-2 pi i m / (2L)) is tw[t] times this, so a transform thread that
 // needs the E entries t + q L/E reads one and forms the others in FP64.
+__device__ constexpr double kCosPi16[9] = {1.0,
+                                           0.98078528040323044913,
+                                           0.92387953251128675613,
+                                           0.83146961230254523708,
+                                           0.70710678118654752440,
+                                           0.55557023301960222474,
+                                           0.38268343236508977173,
+                                           0.19509032201612826785,
+                                           0.0};
 template <int E>
 __device__ __forceinline__ c2<double> root_step(int q) {
   static_assert(E >= 1 && E <= 16 && (E & (E - 1)) == 0, "E: power of two up to 16");
-  constexpr double c[9] = {1.0,
-                           0.98078528040323044913,
-                           0.92387953251128675613,
-                           0.83146961230254523708,
-                           0.70710678118654752440,
-                           0.55557023301960222474,
-                           0.38268343236508977173,
-                           0.19509032201612826785,
-                           0.0};
+  const double* c = kCosPi16;
   const int k = q * (16 / E);  // angle k pi / 16, k < 16
   // cos(k pi/16) = c[k] (k <= 8) or -c[16 - k]; sin(k pi/16) = c[8 - k] or c[k - 8]
   const double cs = k <= 8 ? c[k] : -c[16 - k];
