@@ -275,8 +275,8 @@ int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch)
  * transforms; advect 64 + k and 96 + k (two or one x pairs per thread, nx
  * 256 .. 1024) and mu_source 64 + k (nx 256 .. 2048) = the k-row strip
  * stencil and the row transforms in one kernel (other nx: as k);
- * column_*: block shape 0 .. 4 (8 or 16 values per thread, columns per
- * block); row / row_fwd: shape 0 .. 5 of the inverse / forward row
+ * column_*: block shape 0 .. 4 (4, 8 or 16 values per thread; the pass's two
+ * fields one after the other or side by side); row / row_fwd: shape 0 .. 5 of the inverse / forward row
  * transforms (8 or 4 values per thread; all or a quarter of the rows per
  * block, or 4 and 5: groups of four consecutive rows stored or loaded
  * together)), at most cap

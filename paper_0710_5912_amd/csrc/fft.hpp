@@ -110,7 +110,9 @@ constexpr int bitrev(int i, int bits) {
 // (4096^2 step 840 -> 825 us).  FP32 keeps the separate one: a transform's
 // result shrinks by the rounding of the low-order roots, which a run adds up
 // step after step, and the folded form shrinks more for R <= 8 (512 points:
-// 2.9e-8 per transform against 2.4e-8).
+// 2.9e-8 per transform against 2.4e-8).  For R = 16 it shrinks less (4096 points:
+// 3.2e-8 against 4.7e-8, and 3.0e-8 with R = 8): the column passes, bound by
+// these operations, take it there.
 template <typename T, int R>
 constexpr bool kFolded = sizeof(T) == 8;
 
@@ -343,6 +345,19 @@ __device__ __forceinline__ int lds_slot(int i) {
   return i ^ ((i >> 4) & 15);
 }
 
+// Orders a group's LDS accesses between the steps of a transform.  WAVE: the
+// group lies within one wavefront, whose LDS operations execute in order, so
+// only the compiler has to keep them in order; else a block barrier.
+template <bool WAVE>
+__device__ __forceinline__ void group_sync() {
+  if constexpr (WAVE) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
 // Length-L complex FFT by a group of P = L/E threads; thread t in [0, P).
 // On entry v[q] = x[t + q P]; on exit v[q] = X[t + q P].
 // lds: the group's LDS area, element i at lds[lds_slot<T>(i) * LS].  tw: the FP64 table
@@ -353,18 +368,9 @@ __device__ __forceinline__ int lds_slot(int i) {
 // block must call this with the same L (the passes contain
 // __syncthreads()).  On return other threads may still read lds: barrier
 // before reusing it.
-// TWL: w from ltw, an LDS copy of the table's even entries ltw[i] =
-// tw[2 i], i < L/E (fft_ltw_fill), instead of global memory, for transforms
-// that follow stores of the same thread (a global read would wait for
-// them: a wave's loads and stores share one counter).
-template <int L, int E, int NT>
-__device__ __forceinline__ void fft_ltw_fill(c2<double>* ltw, gp<const c2<double>> __restrict__ tw) {
-  for (int i = threadIdx.x; i < L / E; i += NT) ltw[i] = ldg<double>(tw + 2 * i);
-}
-template <typename T, int L, int E, int DIR, bool TWL = false>
+template <typename T, int L, int E, int DIR>
 __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
-                                          gp<const c2<double>> __restrict__ tw, int t,
-                                          const c2<double>* ltw = nullptr) {
+                                          gp<const c2<double>> __restrict__ tw, int t) {
   constexpr int P = L / E;
   constexpr int R0 = first_radix(L, E);
   constexpr int Q = E / R0;
@@ -388,13 +394,7 @@ __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
   if constexpr (L > R0) {
     constexpr int NP = fft_passes(L, E);
     // entry (2L/E)/Ns (t mod Ns): even, below 2L/E, as Ns <= L/E
-    auto tw_of = [&](int Ns) {
-      const int k = (2 * L / E) / Ns * (t & (Ns - 1));
-      if constexpr (TWL)
-        return ltw[k >> 1];
-      else
-        return ldg<double>(tw + k);
-    };
+    auto tw_of = [&](int Ns) { return ldg<double>(tw + (2 * L / E) / Ns * (t & (Ns - 1))); };
     c2<double> wn = tw_of(R0);
     int Ns = R0;
 #pragma unroll
@@ -418,70 +418,89 @@ __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
   }
 }
 
-// Two independent length-L transforms (v0 in lds0, v1 in lds1) by the same
-// group, pass by pass: each pass of both shares one pair of barriers, and
-// each result equals fft_group's for that array alone (same operations).
-template <typename T, int L, int E, int DIR>
-__device__ __forceinline__ void fft_group2(c2<T>* v0, c2<T>* v1, c2<T>* lds0, c2<T>* lds1,
-                                           int LS, gp<const c2<double>> __restrict__ tw,
-                                           int t) {
+// The passes' twiddles of a kernel that runs several transforms of one length:
+// per pass and thread w = exp(-2 pi i (t mod Ns) / (Ns E)), read from the table
+// once (fft_regs then touches no global memory).  KEEP: what a pass forms from
+// it (PassW) stays in registers (FP32, and up to 8 values in FP64 where LDS and
+// grid leave the registers free); else it is formed at each use, from w in a
+// register or, with LDSW (NT threads), in the thread's own place in LDS.
+template <typename T, int L, int E, int LDSW = 0, bool FOLDED_ = kFolded<T, E>>
+struct PassSet {
+  static constexpr bool FOLDED = FOLDED_;
+  static constexpr int NP = fft_passes(L, E), NPA = NP > 0 ? NP : 1;
+  static constexpr bool KEEP = sizeof(T) == 4 || E <= 4 || (E == 8 && L <= 1024);
+  static constexpr int NLDS = !KEEP && LDSW > 0 ? NPA * LDSW : 1;  // values of `area`
+  c2<double> w[KEEP || LDSW > 0 ? 1 : NPA];
+  PassW<T, E, FOLDED> pw[KEEP ? NPA : 1];
+  c2<double>* area;
+  __device__ __forceinline__ void load(gp<const c2<double>> tw, int t, c2<double>* lds = nullptr) {
+    int Ns = first_radix(L, E);
+    if constexpr (!KEEP && LDSW > 0) area = lds + threadIdx.x;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const c2<double> a = ldg<double>(tw + (2 * L / E) / Ns * (t & (Ns - 1)));
+      if constexpr (KEEP)
+        pw[p].set(a);
+      else if constexpr (LDSW > 0)
+        area[p * LDSW] = a;
+      else
+        w[p] = a;
+      Ns *= E;
+    }
+  }
+  template <int DIR>
+  __device__ __forceinline__ void pass(c2<T>* v, int p) const {
+    if constexpr (KEEP) {
+      dft_tw<T, DIR, E>(v, pw[p]);
+    } else {
+      // opaque, so that the compiler does not keep what it forms from it
+      c2<double> a = LDSW > 0 ? area[p * LDSW] : w[LDSW > 0 ? 0 : p];
+      asm volatile("" : "+v"(a.x), "+v"(a.y));
+      PassW<T, E, FOLDED> f;
+      f.set(a);
+      dft_tw<T, DIR, E>(v, f);
+    }
+  }
+};
+
+// fft_group's transform with the passes' factors from registers and the
+// group's own ordering (WAVE, group_sync).  On return other threads of the
+// group may still read lds.
+template <typename T, int L, int E, int DIR, bool WAVE, typename TW>
+__device__ __forceinline__ void fft_regs(c2<T>* v, c2<T>* lds, int LS, const TW& tw, int t) {
   constexpr int P = L / E;
   constexpr int R0 = first_radix(L, E);
   constexpr int Q = E / R0;
+  constexpr int NP = fft_passes(L, E);
   static_assert(L % E == 0 && E % R0 == 0, "bad FFT factorisation");
+  // values v[i] to elements dst(i), then v[r] = element t + r P
+  auto exchange = [&](auto&& dst) {
+#pragma unroll
+    for (int i = 0; i < E; ++i) lds[lds_slot<T>(dst(i)) * LS] = v[i];
+    group_sync<WAVE>();
+#pragma unroll
+    for (int r = 0; r < E; ++r) v[r] = lds[lds_slot<T>(t + r * P) * LS];
+  };
+  // pass 0: value q + r Q is input r of butterfly t + q P
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
-    c2<T> b0[R0], b1[R0];
+    c2<T> b[R0];
 #pragma unroll
-    for (int r = 0; r < R0; ++r) {
-      b0[r] = v0[q + r * Q];
-      b1[r] = v1[q + r * Q];
-    }
-    dft_reg<T, DIR, R0>(b0);
-    dft_reg<T, DIR, R0>(b1);
-    if constexpr (L == R0) {
+    for (int r = 0; r < R0; ++r) b[r] = v[q + r * Q];
+    dft_reg<T, DIR, R0, TW::FOLDED>(b);
 #pragma unroll
-      for (int r = 0; r < R0; ++r) {
-        v0[r] = b0[r];
-        v1[r] = b1[r];
-      }
-    } else {
-      const int j = t + q * P;
-#pragma unroll
-      for (int r = 0; r < R0; ++r) {
-        lds0[lds_slot<T>(j * R0 + r) * LS] = b0[r];
-        lds1[lds_slot<T>(j * R0 + r) * LS] = b1[r];
-      }
-    }
+    for (int r = 0; r < R0; ++r) v[q + r * Q] = b[r];
   }
   if constexpr (L > R0) {
-    constexpr int NP = fft_passes(L, E);
-    auto tw_of = [&](int Ns) { return ldg<double>(tw + (2 * L / E) / Ns * (t & (Ns - 1))); };
-    c2<double> wn = tw_of(R0);
+    exchange([&](int i) { return (t + (i % Q) * P) * R0 + i / Q; });
     int Ns = R0;
 #pragma unroll
     for (int pass = 0; pass < NP; ++pass) {
-      const c2<double> w = wn;
-      if (pass + 1 < NP) wn = tw_of(Ns * E);
-      __syncthreads();
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        v0[r] = lds0[lds_slot<T>(t + r * P) * LS];
-        v1[r] = lds1[lds_slot<T>(t + r * P) * LS];
-      }
-      PassW<T, E> pw;
-      pw.set(w);
-      dft_tw<T, DIR, E>(v0, pw);
-      dft_tw<T, DIR, E>(v1, pw);
+      tw.template pass<DIR>(v, pass);
       if (pass + 1 == NP) break;
-      __syncthreads();
-      const int k = t & (Ns - 1);
-      const int idxD = (t / Ns) * Ns * E + k;
-#pragma unroll
-      for (int r = 0; r < E; ++r) {
-        lds0[lds_slot<T>(idxD + r * Ns) * LS] = v0[r];
-        lds1[lds_slot<T>(idxD + r * Ns) * LS] = v1[r];
-      }
+      group_sync<WAVE>();
+      const int d = (t / Ns) * Ns * E + (t & (Ns - 1)), n = Ns;
+      exchange([&](int i) { return d + i * n; });
       Ns *= E;
     }
   }

@@ -266,7 +266,7 @@ struct ColLaunch {
   template <int MODE, int VAR, bool BANDED = false>
   static void launch(const Run* runs, int nruns, int nx, const StepArgs* sa, int bin0, int bin1,
                      int bout0, int bout1, hipStream_t st) {
-    using C = ColCfg<T, L, VAR>;
+    using C = ColCfg<T, L, VAR, col_fields(MODE)>;
     const dim3 gr((nx / 2 + 1 + C::CW - 1) / C::CW, 1, nruns), bl(C::THREADS);
     hipLaunchKernelGGL((k_column<T, L, MODE, VAR, BANDED>), gr, bl, 0, st, runs, sa, bin0, bin1,
                        bout0, bout1);

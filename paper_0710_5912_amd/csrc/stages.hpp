@@ -28,17 +28,10 @@ constexpr int col_elems(int L) { return L >= 8 ? 8 : L; }
 
 // Occupancy hint for the stage kernels (waves per SIMD the register
 // allocation must allow).
-#ifndef LE_COL_DUAL
-#define LE_COL_DUAL 1
-#endif
 #ifndef LE_WAVES
 #define LE_WAVES 2
 #endif
-#ifndef LE_WAVES_COL
-#define LE_WAVES_COL LE_WAVES
-#endif
 #define LE_OCCUPANCY __attribute__((amdgpu_waves_per_eu(LE_WAVES)))
-#define LE_OCCUPANCY_COL __attribute__((amdgpu_waves_per_eu(LE_WAVES_COL)))
 // Keep the scheduler from interleaving consecutive unrolled iterations (which
 // would hoist every iteration's loads and blow the register budget).
 #define LE_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
@@ -53,24 +46,35 @@ struct RowCfg {
   static constexpr int THREADS = G * P;
 };
 
-// Column kernel shapes, VAR (a tuning choice, 0 .. 4): E values per thread
-// (8, or 16 for VAR 3 and 4: two register passes fewer LDS exchanges) and
-// CW adjacent columns per block: CW0 = 256/P (VAR 0, 3), twice that (VAR 1,
-// 4) where threads <= 1024 and LDS <= 160 KB allow, or a quarter (VAR 2:
-// more, smaller blocks for grids whose column pass has few blocks).
-template <typename T, int L, int VAR>
+// Column kernel shapes, VAR (a tuning choice, 0 .. 4): E values per thread and
+// SPLIT, the two fields of a pass transformed side by side by two groups of
+// threads (each thread's chain then holds one transform each way) or one after
+// the other by one group.  Blocks are the smallest that fill a wavefront (CW
+// adjacent columns where one column has fewer threads): more, independent
+// blocks overlap one's memory phases with another's transforms better than the
+// same waves behind common barriers (1024^2 FP64 flow pass, E = 8: 14.1 us with
+// one column per block, 15.5 with two, 18.7 with four).  Measured best: E = 16
+// for 4096 points (FP64 CH 92 us, flow 132 us; E = 8 144 and 199), E = 4 or 8
+// for 512 to 2048, the split shapes for grids whose columns leave most SIMDs
+// idle (64^2 flow 3.2 us against 3.8 and, E = 8, 4.5).
+template <typename T, int L, int VAR, int NF = 2>
 struct ColCfg {
-  static constexpr int E = (VAR >= 3 && L >= 16) ? 16 : col_elems(L);
+  static constexpr bool SPLIT = NF == 2 && (VAR == 2 || VAR == 4) && L <= 1024;
+  static constexpr int EV = VAR == 3 ? 16 : ((VAR == 1 || VAR == 2) ? 4 : 8);
+  static constexpr int EL = EV < L ? EV : (L >= 8 ? 8 : L);
+  static constexpr int E = L / EL <= 512 ? EL : (L >= 4096 ? 16 : 8);
   static constexpr int P = L / E;
-  static constexpr int CW0 = clampi(256 / P, 1, 64);
-  static constexpr int CWD = (VAR == 1 || VAR == 4) ? 2 * CW0
-                             : (VAR == 2 ? (CW0 / 4 > 1 ? CW0 / 4 : 1) : CW0);
-  static constexpr bool FITS =
-      CWD <= 64 && CWD * P <= 1024 && (long)CWD * L * (long)sizeof(c2<T>) <= 160L * 1024;
-  static constexpr int CW = FITS ? CWD : CW0;
-  static constexpr int THREADS = CW * P;
+  static constexpr int G = SPLIT ? 2 : 1;  // thread groups
+  // a wavefront's worth of columns; two for a split column of several waves
+  static constexpr int CW = P >= 64 ? (SPLIT ? 2 : 1) : clampi(64 / (G * P), 1, 64);
+  static constexpr int GT = CW * P;        // threads per group
+  static constexpr int THREADS = G * GT;
+  static constexpr bool WAVE = GT <= 64;   // a group lies in one wavefront
+  static_assert(THREADS <= 1024 && (long)G * GT * E * (long)sizeof(c2<T>) <= 160L * 1024, "shape");
 };
 constexpr int kColVariants = 5;
+// Input fields of a column pass.
+constexpr int col_fields(int mode) { return mode == COL_CH || mode == COL_FLOW ? 2 : 1; }
 
 // Observables' column kernel (its LDS also holds the shell partials).
 template <int L>
@@ -182,14 +186,7 @@ __device__ __forceinline__ double rcp64(double x) {
   return fma(r, e, r);
 }
 
-// lambda(q; s) = D + Delta, D = -((1 + s^2) qx^2 + qy^2), Delta = 2 s qx qy:
-// the eigenvalue of the cosheared Laplacian block of Appendix B.
-__device__ __forceinline__ double lambda_of(const Modes& q, double s) {
-  const double D = -((1.0 + s * s) * q.qx * q.qx + q.qy * q.qy);
-  return D + 2.0 * s * q.P;
-}
-
-// The banded scheme switch: the same operator with its y part by the central
+// The banded scheme switch: the cosheared Laplacian with its y part by the central
 // differences of the stencils, i.e. the eigenvalue of the cyclic banded
 // operator of column m on the y wave n:
 //   -(1 + s^2) qx^2 - 4 sin^2(pi n / ny) / dy^2 + 2 s qx sin(2 pi n / ny) / dy,
@@ -1523,133 +1520,144 @@ __global__ void k_copy_real(const Run* __restrict__ run, int bin, int bout) {
 //  COL_FLOW    (omega_h, g) -> (omega', psi')   stages 2b and 3
 //  COL_STOKES  g -> psi'                  zero-Reynolds solve
 //  COL_POISSON omega -> psi               set-up: psi from omega
+// SPLIT (ColCfg): group f of threads transforms field f; between the
+// transforms the groups hand each other their column's values through LDS, and
+// the CH pass's second group ends.  Else one group transforms both, the second
+// field's values requested before the first one's transform where registers
+// allow (the flow pass of 16 values per thread would spill).
 template <typename T, int L, int MODE, int VAR, bool BANDED = false>
-__global__ __launch_bounds__((ColCfg<T, L, VAR>::THREADS)) LE_OCCUPANCY_COL void k_column(
-    const Run* __restrict__ runs, const StepArgs* __restrict__ sa, int bin0, int bin1,
-    int bout0, int bout1) {
-  using C = ColCfg<T, L, VAR>;
+__global__ __launch_bounds__((ColCfg<T, L, VAR, col_fields(MODE)>::THREADS)) LE_OCCUPANCY
+void k_column(const Run* __restrict__ runs, const StepArgs* __restrict__ sa, int bin0, int bin1,
+              int bout0, int bout1) {
+  constexpr int NF = col_fields(MODE);
+  using C = ColCfg<T, L, VAR, NF>;
+  constexpr int E = C::E, P = C::P, CW = C::CW;
+  constexpr bool SPLIT = C::SPLIT, WAVE = C::WAVE;
+  constexpr bool BWAVE = C::THREADS <= 64;  // the whole block is one wavefront
+  constexpr bool BOTH = NF == 2 && !SPLIT;  // one group holds both fields
+  constexpr bool PRE = BOTH && (MODE == COL_CH || E <= 8);
+  __shared__ c2<T> lds[C::G * CW * L];
   const BPos bp = block_pos();
   const Run& R = runs[bp.z];
   const Geo& geo = R.g;
-  auto in0 = bufp<const c2<T>>(R, bin0);
+  const int f = SPLIT ? (int)threadIdx.x / C::GT : 0;
+  const int r = SPLIT ? (int)threadIdx.x % C::GT : (int)threadIdx.x;
+  const int c = r % CW, t = r / CW;
+  auto in = bufp<const c2<T>>(R, f == 0 ? bin0 : bin1);
   auto in1 = bufp<const c2<T>>(R, bin1);
-  auto out0 = bufp<c2<T>>(R, bout0);
-  auto out1 = bufp<c2<T>>(R, bout1);
   auto tw = to_global<const c2<double>>(R.twy);
-  constexpr int NIN = (MODE == COL_CH || MODE == COL_FLOW) ? 2 : 1;
-  constexpr int NOUT = (MODE == COL_FLOW) ? 2 : 1;
-  // Both fields' transforms side by side (one barrier per pass for the two)
-  // where LDS holds two areas: in FP32 and for columns up to 512 values (in
-  // FP64 at 2048 and 4096 the doubled LDS halves the blocks per CU and the
-  // pass runs slower).
-  constexpr bool DUAL = LE_COL_DUAL && NIN == 2 && (sizeof(T) == 4 || L <= 512) &&
-                        2L * C::CW * L * (long)sizeof(c2<T>) <= 160L * 1024;
-  __shared__ c2<T> lds[(DUAL ? 2 : 1) * C::CW * L];
-  c2<T>* const lds1 = lds + (DUAL ? C::CW * L : 0);
-  // the flow pass's second inverse transform follows the first output's
-  // stores: its twiddles come from an LDS copy (fft_group TWL)
-  constexpr bool LTW = MODE == COL_FLOW && !DUAL && L > C::E;
-  __shared__ c2<double> ltw[LTW ? L / C::E : 1];
+  c2<T>* const mine = lds + f * CW * L + c;
   const int S = geo.nx / 2 + 1;
-  const int c = threadIdx.x % C::CW, t = threadIdx.x / C::CW;
-  const int m0 = bp.x * C::CW + c;
+  const int m0 = bp.x * CW + c;
   const bool ok = m0 < S;
   const int m = ok ? m0 : 0;
   // column m of the tiled spectra: element n at col + n kTW
   const size_t col = spec_index(L, 0, m);
-  if constexpr (LTW) fft_ltw_fill<L, C::E, C::THREADS>(ltw, tw);  // read after later barriers
-  c2<T> v0[C::E], v1[C::E];
-  // PRE: the second field's loads are issued before the first field's
-  // transform, so their latency hides behind it.  Only where the registers
-  // already limit the shape to two waves per SIMD (FP64, 16 values per
-  // thread) and the CH pass (the flow pass would spill): elsewhere the
-  // extra registers cost occupancy (measured slower at 1024^2 and 2048^2).
-  constexpr bool PRE = NIN == 2 && !DUAL && MODE == COL_CH && C::E == 16 && sizeof(T) == 8;
+  c2<T> v[E], u[E];  // field f (0 when not SPLIT), the other field
 #pragma unroll
-  for (int q = 0; q < C::E; ++q) v0[q] = ldg<T>(in0 + col + (size_t)(t + q * C::P) * kTW);
-  if constexpr (DUAL || PRE) {
+  for (int q = 0; q < E; ++q) v[q] = ldg<T>(in + col + (size_t)(t + q * P) * kTW);
+  if constexpr (PRE) {
 #pragma unroll
-    for (int q = 0; q < C::E; ++q) v1[q] = ldg<T>(in1 + col + (size_t)(t + q * C::P) * kTW);
+    for (int q = 0; q < E; ++q) u[q] = ldg<T>(in1 + col + (size_t)(t + q * P) * kTW);
   }
-  if constexpr (DUAL) {
-    fft_group2<T, L, C::E, -1>(v0, v1, lds + c, lds1 + c, C::CW, tw, t);
-  } else {
-    fft_group<T, L, C::E, -1>(v0, lds + c, C::CW, tw, t);
-  }
-  if constexpr (NIN == 2 && !DUAL) {
+  // 16 values per thread leave no register for the passes' w in FP64 (LDSW); in
+  // FP32 they take the folded form: 4096^2 CH 53.5 us, flow 68.7 (separate
+  // powers formed at each use 57 and 75, kept in registers 56 and, spilling, 104)
+  typedef PassSet<T, L, E, E == 16 ? C::THREADS : 0, kFolded<T, E> || E == 16> Tw;
+  __shared__ c2<double> wl[Tw::NLDS];
+  Tw ptw;
+  ptw.load(tw, t, wl);
+  fft_regs<T, L, E, -1, WAVE>(v, mine, CW, ptw, t);
+  if constexpr (BOTH) {
     if constexpr (!PRE) {
 #pragma unroll
-      for (int q = 0; q < C::E; ++q) v1[q] = ldg<T>(in1 + col + (size_t)(t + q * C::P) * kTW);
+      for (int q = 0; q < E; ++q) u[q] = ldg<T>(in1 + col + (size_t)(t + q * P) * kTW);
     }
-    __syncthreads();
-    fft_group<T, L, C::E, -1>(v1, lds + c, C::CW, tw, t);
+    group_sync<WAVE>();
+    fft_regs<T, L, E, -1, WAVE>(u, mine, CW, ptw, t);
+  } else if constexpr (SPLIT) {
+    group_sync<BWAVE>();
+    if (MODE == COL_FLOW || f == 1) {
+#pragma unroll
+      for (int q = 0; q < E; ++q) mine[(t + q * P) * CW] = v[q];
+    }
+    group_sync<BWAVE>();
+    if (MODE == COL_CH && f == 1) return;  // (a barrier counts the waves that have not ended)
+#pragma unroll
+    for (int q = 0; q < E; ++q) u[q] = lds[(1 - f) * CW * L + (t + q * P) * CW + c];
   }
   const double s = sa[bp.z].s;
   const double inv_ny = 1.0 / (double)geo.ny;
   const double dtnu = geo.rho > 0.0 ? geo.dt * (geo.eta / geo.rho) : 0.0;
+  // lambda(q; s) = D + Delta, D = -((1 + s^2) qx^2 + qy^2), Delta = 2 s qx qy:
+  // the eigenvalue of the cosheared Laplacian block of Appendix B.  Of the
+  // thread's modes n = t + q P (ny = L), those with q >= E/2 are the negative
+  // waves, and t = 0, q = E/2 is the Nyquist row: five operations a mode.
+  const double qx = geo.kx0 * (double)(m >= geo.nx / 2 ? m - geo.nx : m);
+  const double ax = (1.0 + s * s) * qx * qx, s2 = 2.0 * s;
+  const bool nyq_x = m == geo.nx / 2;
+  auto lambda = [&](int q, int n) {
+    if constexpr (BANDED) return lambda_banded(geo, m, n, s);
+    const double qy = geo.ky0 * (double)(q >= E / 2 ? n - L : n);
+    const double Pxy = (nyq_x || (q == E / 2 && t == 0)) ? 0.0 : qx * qy;
+    return -(ax + qy * qy) + s2 * Pxy;
+  };
 #pragma unroll
-  for (int q = 0; q < C::E; ++q) {
-    const int n = t + q * C::P;
-    const Modes md = modes(geo, m, n);
-    const double lam = BANDED ? lambda_banded(geo, m, n, s) : lambda_of(md, s);
-    const bool zero = (m == 0 && n == 0);
-    const double a0x = (double)v0[q].x, a0y = (double)v0[q].y;
+  for (int q = 0; q < E; ++q) {
+    const int n = t + q * P;
+    const double lam = lambda(q, n);
+    const bool zero = q == 0 && m == 0 && n == 0;
     if constexpr (MODE == COL_CH) {
       // phi' = phi_h + (1 + D4/2)^-1 (-A D2 phi_h - D4 phi_h + B D2 f)
+      const double a0x = (double)v[q].x, a0y = (double)v[q].y;
       const double d2 = geo.dt * geo.M * lam;
       const double d4 = geo.dt * geo.kappa * geo.M * lam * lam;
       const double den = rcp64(1.0 + 0.5 * d4);
       const double h1 = (1.0 + (-geo.A * d2 - d4) * den) * inv_ny;
       const double h2 = (geo.B * d2 * den) * inv_ny;
-      const double a1x = (double)v1[q].x, a1y = (double)v1[q].y;
-      v0[q] = {T(h1 * a0x + h2 * a1x), T(h1 * a0y + h2 * a1y)};
+      const double a1x = (double)u[q].x, a1y = (double)u[q].y;
+      v[q] = {T(h1 * a0x + h2 * a1x), T(h1 * a0y + h2 * a1y)};
     } else if constexpr (MODE == COL_FLOW) {
       // omega' = omega_h + (1 - C/2)^-1 (C omega_h + dt g), C = dt nu lambda;
       // psi' = -omega' / lambda; the q = 0 mode of both is zero.
+      const c2<T> w0 = f == 0 ? v[q] : u[q], w1 = f == 0 ? u[q] : v[q];
+      const double a0x = (double)w0.x, a0y = (double)w0.y;
+      const double a1x = (double)w1.x, a1y = (double)w1.y;
       const double ct = dtnu * lam;
       const double den = rcp64(1.0 - 0.5 * ct);
       double b1 = (1.0 + ct * den) * inv_ny;
       double b2 = (geo.dt * den) * inv_ny;
-      double il = zero ? 0.0 : -rcp64(lam);
       if (zero) { b1 = 0.0; b2 = 0.0; }
-      const double a1x = (double)v1[q].x, a1y = (double)v1[q].y;
+      const double il = zero ? 0.0 : -rcp64(lam);
       const double ox = b1 * a0x + b2 * a1x, oy = b1 * a0y + b2 * a1y;
-      v0[q] = {T(ox), T(oy)};
-      v1[q] = {T(il * ox), T(il * oy)};
+      const c2<T> o0 = {T(ox), T(oy)}, o1 = {T(il * ox), T(il * oy)};
+      v[q] = f == 0 ? o0 : o1;
+      if constexpr (BOTH) u[q] = o1;
     } else if constexpr (MODE == COL_STOKES) {
       // psi' = g / lambda^2
       const double p = zero ? 0.0 : inv_ny * rcp64(lam * lam);
-      v0[q] = {T(p * a0x), T(p * a0y)};
+      v[q] = {T(p * (double)v[q].x), T(p * (double)v[q].y)};
     } else {
       // psi = -omega / lambda
       const double p = zero ? 0.0 : -inv_ny * rcp64(lam);
-      v0[q] = {T(p * a0x), T(p * a0y)};
+      v[q] = {T(p * (double)v[q].x), T(p * (double)v[q].y)};
     }
     LE_SCHED_FENCE();
   }
-  __syncthreads();
-  if constexpr (DUAL && NOUT == 2) {
-    fft_group2<T, L, C::E, +1>(v0, v1, lds + c, lds1 + c, C::CW, tw, t);
-    if (ok) {
-#pragma unroll
-      for (int q = 0; q < C::E; ++q) {
-        stg<T>(out0 + col + (size_t)(t + q * C::P) * kTW, v0[q]);
-        stg<T>(out1 + col + (size_t)(t + q * C::P) * kTW, v1[q]);
-      }
-    }
-    return;
-  }
-  fft_group<T, L, C::E, +1>(v0, lds + c, C::CW, tw, t);
+  group_sync<(SPLIT && MODE == COL_FLOW) ? BWAVE : WAVE>();
+  fft_regs<T, L, E, +1, WAVE>(v, mine, CW, ptw, t);
   if (ok) {
+    auto out = bufp<c2<T>>(R, f == 0 ? bout0 : bout1);
 #pragma unroll
-    for (int q = 0; q < C::E; ++q) stg<T>(out0 + col + (size_t)(t + q * C::P) * kTW, v0[q]);
+    for (int q = 0; q < E; ++q) stg<T>(out + col + (size_t)(t + q * P) * kTW, v[q]);
   }
-  if constexpr (NOUT == 2) {
-    __syncthreads();
-    fft_group<T, L, C::E, +1, LTW>(v1, lds + c, C::CW, tw, t, ltw);
+  if constexpr (BOTH && MODE == COL_FLOW) {
+    group_sync<WAVE>();
+    fft_regs<T, L, E, +1, WAVE>(u, mine, CW, ptw, t);
     if (ok) {
+      auto out = bufp<c2<T>>(R, bout1);
 #pragma unroll
-      for (int q = 0; q < C::E; ++q) stg<T>(out1 + col + (size_t)(t + q * C::P) * kTW, v1[q]);
+      for (int q = 0; q < E; ++q) stg<T>(out + col + (size_t)(t + q * P) * kTW, u[q]);
     }
   }
 }
