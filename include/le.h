@@ -242,6 +242,9 @@ const char* le_last_error(void);
  *   0 inverse row transform of omega and psi    3 inverse row transform of phi
  *   1 advection + forward row transforms (1a)    4 mu and g + forward row transform (2a)
  *   2 column pass, Cahn-Hilliard update (1b)     5 column pass, omega and psi (2b, 3)
+ * Unprofiled steps of most grids join stage 0 to 1 and stage 3 to 4 in one
+ * kernel each; with profiling enabled they stay apart, so that each has a time
+ * of its own (the same step, to rounding).
  * le_profile(c, 1) enables and clears the counters, le_profile(c, 0) disables.
  * le_stage_times writes min(cap, LE_NSTAGES) accumulated milliseconds and
  * launch counts (either pointer may be NULL).
@@ -276,8 +279,8 @@ int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch)
  * 256 .. 1024) and mu_source 64 + k (nx 256 .. 2048) = the k-row strip
  * stencil and the row transforms in one kernel (other nx: as k);
  * column_*: block shape 0 .. 4 (4, 8 or 16 values per thread; the pass's two
- * fields one after the other or side by side); row / row_fwd: shape 0 .. 5 of the inverse / forward row
- * transforms (8 or 4 values per thread; all or a quarter of the rows per
+ * fields one after the other or side by side); row / row_fwd: shape 0 .. 5 of
+ * the inverse / forward row transforms (8 or 4 values per thread; all or a quarter of the rows per
  * block, or 4 and 5: groups of four consecutive rows stored or loaded
  * together)), at most cap
  * values in all, and returns the number of
@@ -291,6 +294,9 @@ int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch)
  * same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
  * that text file across processes, LE_TUNE_CACHE=off times every creation
  * afresh.  Choices fixed through LE_TUNE_* are not cached.
+ * advect, mu_source, row and row_fwd are those of the separate row stages, which
+ * a step runs under le_profile, for the upwind scheme, on rows too long for the
+ * joined kernels, and where LE_TUNE_ADV, _MU, _ROW or _ROW_FWD fixes one.
  */
 enum { LE_TUNING_FIELDS = 10 };
 int le_tuning(le_ctx* c, int32_t* out, int32_t cap);

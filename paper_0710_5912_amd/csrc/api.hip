@@ -77,6 +77,8 @@ double strain_offset_mid(const le_params& p, int64_t n) {
   const double c = p.lx / p.ly;
   return p.gdot * (((double)n + 0.5) * p.dt) - c * (double)wrap_count(p, n);
 }
+// The kernels' values of a step with sawtooth s.
+StepArgs step_args(const le_params& p, double s) { return {s, std::fabs(s) / (p.lx / p.ly)}; }
 #pragma clang fp contract(on)
 
 bool pow2_in(int v, int lo, int hi) { return v >= lo && v <= hi && (v & (v - 1)) == 0; }
@@ -137,6 +139,12 @@ Geo make_geo(const le_params& p) {
   g.dt = p.dt;
   g.kx0 = 6.283185307179586476925286766559 / p.lx;
   g.ky0 = 6.283185307179586476925286766559 / p.ly;
+  g.inv2dx = 1.0 / (2.0 * g.dx);
+  g.inv2dy = 1.0 / (2.0 * g.dy);
+  g.idx2 = 1.0 / (g.dx * g.dx);
+  g.idy2 = 1.0 / (g.dy * g.dy);
+  g.i4dxdy = 1.0 / (4.0 * g.dx * g.dy);
+  g.ninv = -1.0 / (p.rho > 0.0 ? p.rho : p.eta);
   return g;
 }
 
@@ -165,6 +173,8 @@ struct Class {
   int row_variant = 0;       // Ops::row_c2r (inverse row transforms)
   int row_fwd_variant = 0;   // Ops::row_r2c (forward row transforms, also of the
                              // two-kernel stencil stages)
+  int fuse_adv = FUSE_NONE;  // Ops::flow_adv (FUSE_NONE: stages 0 and 1 apart)
+  int fuse_mu = FUSE_NONE;   // Ops::phi_mu (FUSE_NONE: stages 3 and 4 apart)
   bool upwind3 = false;      // LE_SCHEME_UPWIND3: the upwind advection kernel
   bool banded = false;       // LE_SCHEME_BANDED: the banded column kernels
   int advect() const { return upwind3 ? kAdvUpwind : adv_variant; }
@@ -341,8 +351,7 @@ int download_real(Engine* e, const RunHost& r, int b, double* dst) {
 // StepArgs of run r at step n into the table slot d_args[r.internal].
 int set_args_one(Engine* e, const RunHost& r, int64_t n) {
   StepArgs* h = e->h_args + r.internal;
-  h->s = strain_offset(r.p, n);
-  h->pad = 0.0;
+  *h = step_args(r.p, strain_offset(r.p, n));
   LE_TRY(hipMemcpyAsync(e->d_args + r.internal, h, sizeof(StepArgs), hipMemcpyHostToDevice,
                         e->stream));
   return LE_OK;
@@ -366,6 +375,9 @@ int solve_psi(Engine* e, const RunHost& r) {
   return LE_OK;
 }
 
+void enqueue_runs_step(const Class& k, const Run* d, int n, const StepArgs* a, hipStream_t st,
+                       bool inverse = true);
+
 // The stages of one step for every run; sa: the step's row of the table.
 // ev: LE_NSTAGES + 1 events recorded around the stages when timing.
 void enqueue_step(Engine* e, const StepArgs* sa, hipEvent_t* ev) {
@@ -373,6 +385,11 @@ void enqueue_step(Engine* e, const StepArgs* sa, hipEvent_t* ev) {
     if (ev) (void)hipEventRecord(ev[k], e->stream);
   };
   hipStream_t st = e->stream;
+  if (!ev) {
+    for (const Class& k : e->classes)
+      enqueue_runs_step(k, e->d_desc + k.first, (int)k.members.size(), sa + k.first, st);
+    return;
+  }
   mark(0);
   for (const Class& k : e->classes) {
     const Run* d = e->d_desc + k.first;
@@ -499,17 +516,24 @@ int enqueue_chunk(Engine* e, int64_t key, int64_t count, F&& enqueue_one) {
 // with inverse == false the real omega and psi are taken as they are (the
 // inverse row transforms of stage 0 are skipped).
 void enqueue_runs_step(const Class& k, const Run* d, int n, const StepArgs* a, hipStream_t st,
-                       bool inverse = true) {
-  if (inverse) {
+                       bool inverse) {
+  const bool fused = inverse && k.fuse_adv != FUSE_NONE && !k.upwind3;
+  if (fused) {
+    (void)k.ops.flow_adv(d, n, k.ny, a, k.inertial, k.fuse_adv, st);
+  } else if (inverse) {
     if (k.inertial)
       k.ops.row_c2r(d, n, k.ny, B_OM_S, B_OM_R, B_PS_S, B_PS_R, 2, k.row_variant, st);
     else
       k.ops.row_c2r(d, n, k.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1, k.row_variant, st);
   }
-  k.ops.advect(d, n, k.ny, a, k.inertial, k.advect(), k.row_fwd_variant, st);
+  if (!fused) k.ops.advect(d, n, k.ny, a, k.inertial, k.advect(), k.row_fwd_variant, st);
   k.column(COL_CH, d, n, k.nx, a, B_PHIH, B_FH, B_PHIN, B_PHIN, k.col_ch_variant, st);
-  k.ops.row_c2r(d, n, k.ny, B_PHIN, B_PHI, B_PHIN, B_PHI, 1, k.row_variant, st);
-  k.ops.mu_source(d, n, k.ny, a, k.mu_variant, k.row_fwd_variant, st);
+  if (k.fuse_mu != FUSE_NONE) {
+    (void)k.ops.phi_mu(d, n, k.ny, a, k.fuse_mu, st);
+  } else {
+    k.ops.row_c2r(d, n, k.ny, B_PHIN, B_PHI, B_PHIN, B_PHI, 1, k.row_variant, st);
+    k.ops.mu_source(d, n, k.ny, a, k.mu_variant, k.row_fwd_variant, st);
+  }
   if (k.inertial)
     k.column(COL_FLOW, d, n, k.nx, a, B_OMH, B_GH, B_OM_S, B_PS_S, k.col_flow_variant, st);
   else
@@ -794,6 +818,47 @@ void tune_cache_add(const int* key, const int* val) {
   std::fclose(f);
 }
 
+// The form a step's row stages take: the four-pass kernels (fused.hpp) on the
+// grids below, the separate stages elsewhere, under stage timing, for the upwind
+// scheme, and where LE_TUNE_* fixes a variant of theirs.  Measured (us per step,
+// inertial, FP64 / FP32, separate -> four-pass): 64^2 24.0 -> 16.0 / 22.4 ->
+// 14.9, 256^2 26.5 -> 21.2 / 24.3 -> 18.9, 512^2 39.3 -> 30.6 / 32.2 -> 26.2,
+// 1024 x 512 55.8 -> 43.5 / 54.3 -> 33.2, 1024^2 72.1 -> 57.2 / 54.7 -> 49.6,
+// 2048 x 1024 121 -> 105 / 90 -> 72.
+//  * 4 values per thread up to 256-point rows (nx <= 512) while the grid leaves
+//    SIMDs idle: half the serial chain of 8 (256^2 22.3 -> 21.2; 512 x 2048 FP64
+//    66.4 against 73.5 the other way);
+//  * four rows per block re-transform fewer halo rows but need 256 blocks to
+//    fill the chip (1024^2 57.2 against 61.5 with two, 1024 x 512 50.0 against
+//    43.5);
+//  * 16 KB rows (nx = 2048 FP64) leave one block per CU: worth it only where the
+//    separate mu stage has no strip form, nx > ny (2048 x 1024 121 -> 105,
+//    2048^2 197 -> 200), the advection from 512 rows on (2048 x 256 59.1 ->
+//    59.7); longer rows do not fit.
+void fuse_shapes(Class* k) {
+  const int nx = k->nx, ny = k->ny;
+  const bool f64 = k->prec == LE_FP64;
+  int a = FUSE_NONE, m = FUSE_NONE;
+  if (nx <= 256 || (nx == 512 && (ny <= 256 || (f64 && ny <= 1024)))) {
+    a = m = FUSE_2N;
+  } else if (nx <= 1024 || (nx == 2048 && !f64)) {
+    a = m = nx >= 1024 && ny >= 1024 ? FUSE_4W : FUSE_2W;
+  } else if (nx == 2048 && ny < nx) {
+    if (ny >= 512) a = FUSE_2W;
+    m = ny >= 1024 ? FUSE_4W : FUSE_2W;
+  }
+  const bool fa = a && k->ops.flow_adv(nullptr, 0, ny, nullptr, k->inertial, a, nullptr);
+  const bool fm = m && k->ops.phi_mu(nullptr, 0, ny, nullptr, m, nullptr);
+  k->fuse_adv = fa ? a : FUSE_NONE;
+  k->fuse_mu = fm ? m : FUSE_NONE;
+}
+
+// Whether LE_TUNE_* fixes a variant of the separate row stages.
+bool variants_forced() {
+  return env_variant("LE_TUNE_ADV") >= 0 || env_variant("LE_TUNE_MU") >= 0 ||
+         env_variant("LE_TUNE_ROW") >= 0 || env_variant("LE_TUNE_ROW_FWD") >= 0;
+}
+
 int autotune(Engine* e) {
   hipEvent_t a = nullptr, b = nullptr;
   if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) {
@@ -1017,6 +1082,8 @@ int create_engine(int32_t n, const le_params* ps, const double* const* phi0s,
     if (!rc) rc = solve_psi(e, r);
   }
   if (!rc) rc = autotune(e);
+  if (!variants_forced())
+    for (Class& k : e->classes) fuse_shapes(&k);
   if (!rc && e->classes.size() > 1 && !(std::getenv("LE_CLASS_STREAMS") &&
                                         std::getenv("LE_CLASS_STREAMS")[0] == '0')) {
     if (hipEventCreateWithFlags(&e->fork_ev, hipEventDisableTiming) != hipSuccess)
@@ -1059,8 +1126,8 @@ int step_engine(Engine* e, int64_t nsteps) {
       bool wrap = false;
       for (const RunHost& r : e->runs) {
         StepArgs& a = e->h_args[(size_t)k * row + r.internal];
-        a.s = e->midpoint_s ? strain_offset_mid(r.p, n0 + k) : strain_offset(r.p, n0 + k);
-        a.pad = 0.0;
+        a = step_args(r.p, e->midpoint_s ? strain_offset_mid(r.p, n0 + k)
+                                         : strain_offset(r.p, n0 + k));
         wrap = wrap || wrap_count(r.p, n0 + k + 1) != wrap_count(r.p, n0 + k);
       }
       if (wrap) {
@@ -1157,9 +1224,8 @@ int corrected_steps(Engine* e, int64_t ncoarse) {
     const int64_t cap = e->profiling ? kProfChunk : (e->use_graphs ? kGraphChunk : kChunkCap);
     int64_t count = remaining < cap ? remaining : cap;
     for (int64_t k = 0; k < count; ++k) {
-      e->h_args[k].s =
-          e->midpoint_s ? strain_offset_mid(r.p, n0 + k) : strain_offset(r.p, n0 + k);
-      e->h_args[k].pad = 0.0;
+      e->h_args[k] = step_args(r.p, e->midpoint_s ? strain_offset_mid(r.p, n0 + k)
+                                                   : strain_offset(r.p, n0 + k));
       if (wrap_count(r.p, n0 + k + 1) != wrap_count(r.p, n0 + k)) {
         count = k + 1;
         break;
@@ -1388,7 +1454,7 @@ __global__ void k_step_args(StepArgs* __restrict__ out, int count, long long n0,
   const double X = gdot * ((double)(n0 + k) * dt);
   const double w = floor((X + 0.5 * c) / c);
   out[k].s = X - c * w;
-  out[k].pad = 0.0;
+  out[k].w = fabs(out[k].s) / c;
 }
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -1464,6 +1530,7 @@ int step_noalloc(const le_params* pp, double* phi, double* omega, double* psi, i
   // more of the chip idle (256^2: CH 4.5 us against 5.2 to 6.9, flow 5.0
   // against 5.3 to 8.6)
   k.col_ch_variant = k.col_flow_variant = 1;
+  fuse_shapes(&k);
   Run h;
   h.g = make_geo(p);
   for (int b = 0; b < NBUF; ++b) h.buf[b] = o_buf[b] ? sc + o_buf[b] : nullptr;
@@ -2059,6 +2126,11 @@ void le_batch_destroy(le_batch* b) {
 
 namespace le {
 bool get_ops(int precision, int nx, int ny, Ops* ops) {
-  return precision == LE_FP64 ? get_ops_f64(nx, ny, ops) : get_ops_f32(nx, ny, ops);
+  if (!(precision == LE_FP64 ? get_ops_f64(nx, ny, ops) : get_ops_f32(nx, ny, ops))) return false;
+  if (precision == LE_FP64)
+    set_fused_f64(nx, ops);
+  else
+    set_fused_f32(nx, ops);
+  return true;
 }
 }  // namespace le

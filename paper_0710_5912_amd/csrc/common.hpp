@@ -16,12 +16,16 @@ struct Geo {
   double lx, ly, dx, dy, c;   // c = lx / ly, the sawtooth jump
   double A, B, kappa, M, eta, rho, dt;
   double kx0, ky0;   // 2 pi / lx, 2 pi / ly (wavenumber quanta)
+  // what every thread of a stencil kernel would divide for:
+  double inv2dx, inv2dy;      // 1 / (2 dx), 1 / (2 dy)
+  double idx2, idy2, i4dxdy;  // 1 / dx^2, 1 / dy^2, 1 / (4 dx dy)
+  double ninv;                // -1 / rho, or -1 / eta on the Stokes branch
 };
 
 // Per-step values computed by the host shear clock.
 struct StepArgs {
   double s;       // sawtooth strain offset s_n used by every operator of step n
-  double pad;
+  double w;       // |s_n| / c, the weight of the sheared stencil's diagonal part
 };
 
 // Device buffers of one run (storage type T, as void*).

@@ -36,6 +36,10 @@ constexpr int kAdvBatch = 128, kAdvBatch2 = 192, kAdvBatch3 = 256;
 // switch LE_SCHEME_UPWIND3 (stencil kernel, then the forward row transforms).
 constexpr int kAdvUpwind = 1024;
 
+// Shapes of the four-pass row kernels: rows per block, and 4 (N) or 8 to 16 (W)
+// values per thread.
+enum FuseShape { FUSE_NONE = 0, FUSE_2N, FUSE_2W, FUSE_4W };
+
 struct Ops {
   // row transforms; variant (a tuning choice): 0 = 8 values per thread, 1 = 4
   void (*row_r2c)(const Run* runs, int nruns, int ny, int bin, int bout, int variant,
@@ -61,6 +65,13 @@ struct Ops {
   // the transform in one kernel
   void (*mu_source)(const Run* runs, int nruns, int ny, const StepArgs* sa, int variant,
                     int row_variant, hipStream_t st);
+  // the four-pass step's row kernels (fused.hpp): stages 0 and 1, and stages 3
+  // and 4, in a FuseShape; false, and nothing launched, where the shape does
+  // not fit the row length (nruns = 0 only asks); null for nx = 4096
+  bool (*flow_adv)(const Run* runs, int nruns, int ny, const StepArgs* sa, bool inertial,
+                   int shape, hipStream_t st);
+  bool (*phi_mu)(const Run* runs, int nruns, int ny, const StepArgs* sa, int shape,
+                 hipStream_t st);
   // column transform + per-mode update (ColMode) + inverse column transform;
   // variant 0 .. kColVariants-1 picks the block shape
   void (*column)(int mode, const Run* runs, int nruns, int nx, const StepArgs* sa, int bin0,
@@ -81,6 +92,9 @@ struct Ops {
 bool get_ops(int precision, int nx, int ny, Ops* ops);
 bool get_ops_f64(int nx, int ny, Ops* ops);
 bool get_ops_f32(int nx, int ny, Ops* ops);
+// The four-pass row kernels of a row length (their own translation units).
+void set_fused_f64(int nx, Ops* ops);
+void set_fused_f32(int nx, Ops* ops);
 
 // Final reductions of the observables' partials into out (OBS_NTOTAL sums,
 // then nbins shell sums, then nbins shell weights); gsum: scratch of

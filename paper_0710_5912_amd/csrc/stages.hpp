@@ -485,14 +485,13 @@ struct Stencil {
 };
 
 template <typename T>
-__device__ __forceinline__ Stencil<T> make_stencil(const Geo& g, double s) {
+__device__ __forceinline__ Stencil<T> make_stencil(const Geo& g, const StepArgs& a) {
   Stencil<T> st;
-  const double w = fabs(s) / g.c;
-  st.inv2dx = T(1.0 / (2.0 * g.dx));
-  st.inv2dy = T(1.0 / (2.0 * g.dy));
-  st.w = T(w);
-  st.wm = T(1.0 - w);
-  st.off = s >= 0.0 ? g.r : -g.r;
+  st.inv2dx = T(g.inv2dx);
+  st.inv2dy = T(g.inv2dy);
+  st.w = T(a.w);
+  st.wm = T(1.0 - a.w);
+  st.off = a.s >= 0.0 ? g.r : -g.r;
   return st;
 }
 
@@ -648,7 +647,7 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) LE_OCCUPANCY void k_bracket(
       v[q] = {p.x * p.x * p.x, p.y * p.y * p.y};
     }
   } else {
-    const Stencil<T> st = make_stencil<T>(geo, sa[bp.z].s);
+    const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
     auto fb = bufp<const T>(R, job.b);
     auto a_p = fa + (size_t)jp * NX;
     auto a_m = fa + (size_t)jm * NX;
@@ -657,7 +656,7 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) LE_OCCUPANCY void k_bracket(
     auto b_m = fb + (size_t)jm * NX;
     const bool adv = job.kind != JOB_SOURCE;
     const T alpha = adv ? T(1) : T(0);
-    const T beta = adv ? T(-geo.dt) : T(-1.0 / (geo.rho > 0.0 ? geo.rho : geo.eta));
+    const T beta = adv ? T(-geo.dt) : T(geo.ninv);
 #pragma unroll
     for (int q = 0; q < C::E; ++q) {
       const int x = 2 * (t + q * C::P);
@@ -749,7 +748,7 @@ __global__ __launch_bounds__(strip_threads(NX)) void k_adv_strip(
   auto o_phi = bufp<T>(R, B_TMP);
   auto o_f = bufp<T>(R, B_R1);
   auto o_om = bufp<T>(R, B_R2);
-  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z].s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
   const T dt = T(geo.dt);
   const bool fh = geo.f_half != 0;
   const bool inr = inertial != 0;
@@ -901,7 +900,7 @@ __global__ __launch_bounds__(NX / 2 / SEG) void k_adv_strip_fft(const Run* __res
   auto psi = bufp<const T>(R, B_PS_R);
   auto om = bufp<const T>(R, B_OM_R);
   auto tw = to_global<const c2<double>>(R.twx);
-  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z].s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
   const T dt = T(geo.dt);
   const bool fh = geo.f_half != 0;
   const bool inr = inertial != 0;
@@ -1048,7 +1047,7 @@ __global__ __launch_bounds__((AdvBatch<T, NX, NR, EF_>::TPB)) void k_adv_batch(
   auto om = bufp<const T>(R, B_OM_R);
   auto tw = to_global<const c2<double>>(R.twx);
   tw_tab_fill<L, TPB>(wtab, tw);  // read after the loop's first barrier
-  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z].s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
   const T dt = T(geo.dt);
   const bool fh = geo.f_half != 0;
   // fields [f0, f1): 0: phi_h from (phi, psi); 1: f from phi (phi_h when
@@ -1190,6 +1189,10 @@ template <typename T>
 struct MuCoef {
   T cxx, cyy, cxy, A, B, kap;
 };
+template <typename T>
+__device__ __forceinline__ MuCoef<T> make_mu(const Geo& g, double s) {
+  return {T((1.0 + s * s) * g.idx2), T(g.idy2), T(-2.0 * s * g.i4dxdy), T(g.A), T(g.B), T(g.kappa)};
+}
 // mu at one point from the 3x3 phi neighbourhood (rows d, c, u = j-1, j, j+1;
 // columns w, m, e = x-1, x, x+1).
 template <typename T>
@@ -1231,10 +1234,9 @@ __global__ __launch_bounds__(strip_threads(NX)) void k_mug_strip(
   auto phi = bufp<const T>(R, B_PHI);
   auto o_g = bufp<T>(R, B_TMP);
   const double s = sa[bp.z].s;
-  const MuCoef<T> k = {T((1.0 + s * s) / (geo.dx * geo.dx)), T(1.0 / (geo.dy * geo.dy)),
-                       T(-2.0 * s / (4.0 * geo.dx * geo.dy)), T(geo.A), T(geo.B), T(geo.kappa)};
-  const Stencil<T> st = make_stencil<T>(geo, s);
-  const T neg_inv = T(-1.0 / (geo.rho > 0.0 ? geo.rho : geo.eta));
+  const MuCoef<T> k = make_mu<T>(geo, s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
+  const T neg_inv = T(geo.ninv);
   auto row = [&](int j) {  // j in [-2, ny + 4]: one wrap at most, no division
     return phi + (size_t)(j < 0 ? j + ny : (j >= ny ? j - ny : j)) * NX;
   };
@@ -1287,10 +1289,9 @@ __global__ __launch_bounds__(NX / 2) void k_mug_strip_fft(const Run* __restrict_
   auto out = bufp<c2<T>>(R, B_GH);
   auto tw = to_global<const c2<double>>(R.twx);
   const double s = sa[bp.z].s;
-  const MuCoef<T> k = {T((1.0 + s * s) / (geo.dx * geo.dx)), T(1.0 / (geo.dy * geo.dy)),
-                       T(-2.0 * s / (4.0 * geo.dx * geo.dy)), T(geo.A), T(geo.B), T(geo.kappa)};
-  const Stencil<T> st = make_stencil<T>(geo, s);
-  const T neg_inv = T(-1.0 / (geo.rho > 0.0 ? geo.rho : geo.eta));
+  const MuCoef<T> k = make_mu<T>(geo, s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
+  const T neg_inv = T(geo.ninv);
   const int grp = threadIdx.x / PF, tt = threadIdx.x % PF;
   auto row = [&](int j) {  // j in [-2, ny + 4]: one wrap at most, no division
     return phi + (size_t)(j < 0 ? j + ny : (j >= ny ? j - ny : j)) * NX;
@@ -1358,10 +1359,9 @@ __global__ __launch_bounds__((AdvBatch<T, NX, NR, EF_>::TPB)) void k_mug_batch(
   auto tw = to_global<const c2<double>>(R.twx);
   tw_tab_fill<L, TPB>(wtab, tw);  // read after the loop's first barrier
   const double s = sa[bp.z].s;
-  const MuCoef<T> k = {T((1.0 + s * s) / (geo.dx * geo.dx)), T(1.0 / (geo.dy * geo.dy)),
-                       T(-2.0 * s / (4.0 * geo.dx * geo.dy)), T(geo.A), T(geo.B), T(geo.kappa)};
-  const Stencil<T> st = make_stencil<T>(geo, s);
-  const T neg_inv = T(-1.0 / (geo.rho > 0.0 ? geo.rho : geo.eta));
+  const MuCoef<T> k = make_mu<T>(geo, s);
+  const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
+  const T neg_inv = T(geo.ninv);
   const int grp = threadIdx.x / PF, tt = threadIdx.x % PF;
   auto row = [&](int j) {  // j in [-2, ny + 4]: one wrap at most, no division
     return phi + (size_t)(j < 0 ? j + ny : (j >= ny ? j - ny : j)) * NX;
@@ -1428,10 +1428,8 @@ __global__ __launch_bounds__(RowCfg<L>::THREADS) LE_OCCUPANCY void k_mu(
   auto phi = bufp<const T>(R, bin);
   auto mu = bufp<T>(R, bout) + (size_t)j * NX;
   const double s = sa[bp.z].s;
-  const T cxx = T((1.0 + s * s) / (geo.dx * geo.dx));
-  const T cyy = T(1.0 / (geo.dy * geo.dy));
-  const T cxy = T(-2.0 * s / (4.0 * geo.dx * geo.dy));
-  const T A = T(geo.A), B = T(geo.B), kap = T(geo.kappa);
+  const MuCoef<T> k = make_mu<T>(geo, s);
+  const T cxx = k.cxx, cyy = k.cyy, cxy = k.cxy, A = k.A, B = k.B, kap = k.kap;
   const T two = T(2);
   auto p_c = phi + (size_t)j * NX;
   auto p_p = phi + (size_t)jp * NX;
