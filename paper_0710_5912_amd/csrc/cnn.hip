@@ -12,11 +12,27 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+// wide loads from a caller's arrays, which need only their elements' alignment
+typedef unsigned short u16x8_any __attribute__((ext_vector_type(8), aligned(2)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+typedef unsigned u32_any __attribute__((aligned(2)));
 
 constexpr int kOffW[kCnnLayers] = {0, 608, 9856, 19104};
 constexpr int kOffB[kCnnLayers] = {576, 9824, 19072, 19680};
 
+// A training step takes as many samples at once as hold kGroupPixels pixels
+// (850 B each; 16 of 256^2: 733 us per step, in groups of 8 765, of 4 862).
+// Blocks over the tiles of a batch: three per CU, as many as are resident, of
+// the 32-channel forward (1024 blocks: 66 -> 64 us, last layer 38 -> 32), four
+// of the others; of the weight gradient as many as are resident, so that its
+// partials (37 KB per block in the middle layers) are few.
+constexpr int kGroupPixels = 1 << 20;
+constexpr int kFwdBlocks = 768, kConvBlocks = 1024;
+constexpr int kDwBlocks[kCnnLayers] = {1024, 512, 512, 1024};
+
 constexpr int pad16(int k) { return (k + 15) / 16 * 16; }
+constexpr int pad32(int k) { return (k + 31) / 32 * 32; }
 
 // FP32 -> BF16, round to nearest even (the hardware conversion).
 __device__ __forceinline__ uint16_t f2bf(float f) {
@@ -50,61 +66,133 @@ __device__ __forceinline__ int nb(int p, int dy, int dx, int H, int W, int lgW) 
   return (((py + dy) & (H - 1)) << lgW) | ((px + dx) & (W - 1));
 }
 
+// ---------------------------------------------------------------- tiles
+//
+// The per-layer kernels take tiles of 16 x 16 pixels in turn (ntiles over all
+// samples) and stage each tile's operands, with one pixel of halo, once in LDS
+// as BF16: every pixel is then read about once from memory instead of once per
+// tap, and a batch is one launch per layer.
+
+constexpr int kFT = 16, kFS = 40;   // LDS pixel stride of 32 channels: the 80 bytes
+                                    // put 16-byte reads of consecutive pixels on
+                                    // distinct banks
+constexpr int kHR = kFT + 2;
+
+struct TileAt {
+  int y0, x0;
+  size_t base;   // the sample's first pixel
+};
+__device__ __forceinline__ TileAt tile_at(int tile, int H, int W, int lgW) {
+  const int tiles_x = W / kFT, tps = tiles_x * (H / kFT);
+  const int smp = tile / tps, k = tile - smp * tps;
+  return {k / tiles_x * kFT, k % tiles_x * kFT, (size_t)smp * ((size_t)H << lgW)};
+}
+// Pixel q of the tile with its halo, row by row.
+__device__ __forceinline__ size_t halo_px(const TileAt& at, int q, int H, int W, int lgW) {
+  const int y = (at.y0 - 1 + q / kHR) & (H - 1), x = (at.x0 - 1 + q % kHR) & (W - 1);
+  return at.base + (size_t)((y << lgW) + x);
+}
+// Pixel pp of the tile's 256.
+__device__ __forceinline__ size_t tile_px(const TileAt& at, int pp, int lgW) {
+  return at.base + (size_t)(((at.y0 + (pp >> 4)) << lgW) + at.x0 + (pp & 15));
+}
+
+// Eight k values, k = tap C + channel, of output pixel (oy, ox) for MFMA step
+// ks from the staged tile; FLIP reads the taps mirrored (the input gradient).
+template <int C, bool FLIP>
+__device__ __forceinline__ u16x8 tile_operand(const uint16_t* in, int oy, int ox, int ks,
+                                              int half) {
+  auto off = [](int tap) {
+    return FLIP ? (2 - tap / 3) * kHR + 2 - tap % 3 : tap / 3 * kHR + tap % 3;
+  };
+  u16x8 av;
+  if constexpr (C == 2) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int ta = ks * 8 + e, tb = ta + 4;   // the tap of each half
+      const int oa = ta < 9 ? off(ta) : 0, ob = tb < 9 ? off(tb) : 0;
+      unsigned v = 0;
+      if (half ? tb < 9 : ta < 9)
+        v = *reinterpret_cast<const unsigned*>(in + 2 * (oy * kHR + ox + (half ? ob : oa)));
+      av[2 * e] = (uint16_t)(v & 0xffffu);
+      av[2 * e + 1] = (uint16_t)(v >> 16);
+    }
+  } else {
+    av = *reinterpret_cast<const u16x8*>(in + (oy * kHR + ox + off(ks / 2)) * kFS +
+                                         (ks & 1) * 16 + half * 8);
+  }
+  return av;
+}
+
 // ---------------------------------------------------------------- forward
 
 // z[p][co] = b[co] + sum_{tap, ci} W[co][ci][tap] a[p + tap - (1,1)][ci];
-// a_out = bf16(silu(z)) when ACT.  Block: 4 waves, each a 32-pixel tile.
+// a_out = bf16(silu(z)) when ACT.  Four wavefronts, each two 32-pixel products
+// per tile.  Bound by memory, mostly its writes: 2^20 pixels take 36 us (2 -> 32
+// channels, 200 B per pixel), 64 us (32 -> 32, 270 B) and 32 us (32 -> 2).
 template <int CIN, int COUT, bool ACT>
 __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ a_in,
                                                   const uint16_t* __restrict__ wt,
                                                   const float* __restrict__ bias,
                                                   float* __restrict__ z_out,
-                                                  uint16_t* __restrict__ a_out, int H, int W,
-                                                  int lgW) {
-  constexpr int K = 9 * CIN, KP = pad16(K);
+                                                  uint16_t* __restrict__ a_out, int ntiles,
+                                                  int H, int W, int lgW) {
+  constexpr int KP = pad16(9 * CIN), NKS = KP / 16;
+  __shared__ __align__(16) uint16_t in[kHR * kHR * (CIN == 2 ? 2 : kFS)];
   const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
-  const int p0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-  const int p = p0 + i;
-  f32x16 acc = {};
-  // every operand of the tile is requested before the first product: at
-  // 32 pixels per wavefront a 256^2 grid gives only ~2 wavefronts per SIMD,
-  // too few to hide a load per k step
-  constexpr int NKS = KP / 16;
-  u16x8 av[NKS], bv[NKS];
+  u16x8 bv[NKS];
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) {
-    const int k0 = ks * 16 + half * 8;
-    if constexpr (CIN % 8 == 0) {
-      const int tap = k0 / CIN, ci0 = k0 % CIN;
-      const int q = nb(p, tap / 3 - 1, tap % 3 - 1, H, W, lgW);
-      av[ks] = *reinterpret_cast<const u16x8*>(a_in + (size_t)q * CIN + ci0);
+  for (int ks = 0; ks < NKS; ++ks)
+    bv[ks] = *reinterpret_cast<const u16x8*>(wt + (size_t)i * KP + ks * 16 + half * 8);
+  const float bc = i < COUT ? bias[i] : 0.f;
+  constexpr int G = CIN == 2 ? 1 : 4, NI = kHR * kHR * G, NT = (NI + 255) / 256;
+  for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
+    const TileAt at = tile_at(tile, H, W, lgW);
+    if constexpr (CIN == 2) {
+      unsigned v[NT];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int q = (int)threadIdx.x + u * 256;
+        if (q < NI) v[u] = *reinterpret_cast<const u32_any*>(a_in + halo_px(at, q, H, W, lgW) * 2);
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int q = (int)threadIdx.x + u * 256;
+        if (q < NI) *reinterpret_cast<unsigned*>(in + 2 * q) = v[u];
+      }
     } else {
+      u16x8 v[NT];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = k0 + e;
-        uint16_t v = 0;
-        if (k < K) {
-          const int tap = k / CIN, ci = k % CIN;
-          v = a_in[(size_t)nb(p, tap / 3 - 1, tap % 3 - 1, H, W, lgW) * CIN + ci];
-        }
-        av[ks][e] = v;
+      for (int u = 0; u < NT; ++u) {
+        const int it = (int)threadIdx.x + u * 256;
+        if (it < NI)
+          v[u] = *reinterpret_cast<const u16x8*>(a_in + halo_px(at, it / G, H, W, lgW) * CIN +
+                                                 it % G * 8);
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int it = (int)threadIdx.x + u * 256;
+        if (it < NI) *reinterpret_cast<u16x8*>(in + it / G * kFS + it % G * 8) = v[u];
       }
     }
-    bv[ks] = *reinterpret_cast<const u16x8*>(wt + (size_t)i * KP + k0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    for (int mt = (int)(threadIdx.x >> 6); mt < kFT * kFT / 32; mt += 4) {
+      const int t = mt * 32 + i;
+      f32x16 acc = {};
 #pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) acc = mfma(av[ks], bv[ks], acc);
-  const int co = i;
-  if (co < COUT) {
-    const float bc = bias[co];
+      for (int ks = 0; ks < NKS; ++ks)
+        acc = mfma(tile_operand<CIN, false>(in, t >> 4, t & 15, ks, half), bv[ks], acc);
+      if (i < COUT) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int pp = p0 + c_row(r, half);
-      const float z = acc[r] + bc;
-      z_out[(size_t)pp * COUT + co] = z;
-      if constexpr (ACT) a_out[(size_t)pp * COUT + co] = f2bf(silu(z));
+        for (int r = 0; r < 16; ++r) {
+          const size_t e = tile_px(at, mt * 32 + c_row(r, half), lgW) * COUT + i;
+          const float z = acc[r] + bc;
+          z_out[e] = z;
+          if constexpr (ACT) a_out[e] = f2bf(silu(z));
+        }
+      }
     }
+    __syncthreads();
   }
 }
 
@@ -118,20 +206,22 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ a
 // computes the (22 - 2l)^2 pixels the next layer needs.  Each value is formed
 // with the k order, products and roundings of the per-layer kernel above, so
 // it equals the per-layer result bit for bit.
-constexpr int kFT = 16, kFH = 4, kFR = kFT + 2 * kFH, kFS = 40, kFWaves = 8;
+constexpr int kFH = 4, kFR = kFT + 2 * kFH, kFWaves = 8;
 
 // One layer on the tile: input region SIN x SIN (LDS), output region
 // (SIN - 2)^2, weights wt in LDS as [COUT][KP + 8] (the 8 of padding spread
-// the rows over the banks).  Hidden layers write bf16(silu(z)) to LDS; the last writes z
-// of both channels to z_out at the global pixels (tile origin gy0, gx0) and
-// adds channel 0 into zs (FP64, lanes 0 and 32 of each wavefront).
+// the rows over the banks).  Hidden layers write bf16(silu(z)) to LDS, whole
+// 32-pixel tiles of it (a mask per value kept the exponentials of different
+// values apart: 256^2 14.0 us per call, without 12.8); the last writes z of both
+// channels to z_out at the global pixels (tile origin gy0, gx0) and adds channel
+// 0 into zs (FP64, lanes 0 and 32 of each wavefront).
 template <int CIN, int SIN, bool LAST>
 __device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in,
                                             uint16_t* __restrict__ out,
                                             const uint16_t* __restrict__ wt,
                                             const float* __restrict__ bias,
-                                            float* __restrict__ z_out, int gy0, int gx0, int H,
-                                            int W, int lgW, double& zs) {
+                                            float* __restrict__ z_out, int gy0, int gx0, int lgW,
+                                            double& zs) {
   constexpr int COUT = LAST ? 2 : 32;
   constexpr int SOUT = SIN - 2, NP = SOUT * SOUT, NT = (NP + 31) / 32;
   constexpr int K = 9 * CIN, KP = pad16(K), NKS = KP / 16;
@@ -171,21 +261,18 @@ __device__ __forceinline__ void fused_layer(const uint16_t* __restrict__ in,
     f32x16 acc = {};
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) acc = mfma(av[ks], bv[ks], acc);
-    if (i < COUT) {
+    if constexpr (!LAST) {
+      // rows past the region land in the buffer's padding
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        out[(tile * 32 + c_row(r, half)) * kFS + i] = f2bf(silu(acc[r] + bc));
+    } else if (i < COUT) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int tt = tile * 32 + c_row(r, half);
-        if (tt < NP) {
-          const float z = acc[r] + bc;
-          if constexpr (!LAST) {
-            out[tt * kFS + i] = f2bf(silu(z));
-          } else {
-            const int y = tt / SOUT, x = tt - y * SOUT;
-            const int gp = (((gy0 + y) & (H - 1)) << lgW) | ((gx0 + x) & (W - 1));
-            z_out[(size_t)gp * 2 + i] = z;
-            if (i == 0) zs += (double)z;
-          }
-        }
+        const float z = acc[r] + bc;
+        z_out[(size_t)(((gy0 + tt / kFT) << lgW) + gx0 + tt % kFT) * 2 + i] = z;
+        if (i == 0) zs += (double)z;
       }
     }
   }
@@ -202,8 +289,8 @@ __global__ __launch_bounds__(kFWaves * 64) void k_net_fused(
     const float* __restrict__ params, float* __restrict__ z3, double* __restrict__ part, int H,
     int W, int lgW) {
   __shared__ __align__(16) uint16_t in0[kFR * kFR * 2];
-  __shared__ __align__(16) uint16_t buf_a[(kFR - 2) * (kFR - 2) * kFS];
-  __shared__ __align__(16) uint16_t buf_b[(kFR - 4) * (kFR - 4) * kFS];
+  __shared__ __align__(16) uint16_t buf_a[pad32((kFR - 2) * (kFR - 2)) * kFS];
+  __shared__ __align__(16) uint16_t buf_b[pad32((kFR - 4) * (kFR - 4)) * kFS];
   constexpr int KP0 = pad16(18), KP = pad16(288);
   __shared__ __align__(16) uint16_t wl0[32 * (KP0 + 8)];
   __shared__ __align__(16) uint16_t wl1[32 * (KP + 8)];
@@ -268,16 +355,16 @@ __global__ __launch_bounds__(kFWaves * 64) void k_net_fused(
   }
   __syncthreads();
   double zs = 0.0;
-  fused_layer<2, kFR, false>(in0, buf_a, wl0, params + kOffB[0], nullptr, 0, 0, H, W, lgW, zs);
+  fused_layer<2, kFR, false>(in0, buf_a, wl0, params + kOffB[0], nullptr, 0, 0, lgW, zs);
   __syncthreads();
-  fused_layer<32, kFR - 2, false>(buf_a, buf_b, wl1, params + kOffB[1], nullptr, 0, 0, H, W,
-                                  lgW, zs);
+  fused_layer<32, kFR - 2, false>(buf_a, buf_b, wl1, params + kOffB[1], nullptr, 0, 0, lgW,
+                                  zs);
   __syncthreads();
-  fused_layer<32, kFR - 4, false>(buf_b, buf_a, wl2, params + kOffB[2], nullptr, 0, 0, H, W,
-                                  lgW, zs);
+  fused_layer<32, kFR - 4, false>(buf_b, buf_a, wl2, params + kOffB[2], nullptr, 0, 0, lgW,
+                                  zs);
   __syncthreads();
-  fused_layer<32, kFR - 6, true>(buf_a, nullptr, wl3, params + kOffB[3], z3, ty0, tx0, H, W,
-                                 lgW, zs);
+  fused_layer<32, kFR - 6, true>(buf_a, nullptr, wl3, params + kOffB[3], z3, ty0, tx0, lgW,
+                                 zs);
   const int lane = threadIdx.x & 63;
   if ((lane & 31) == 0) wsum[(threadIdx.x >> 6) * 2 + (lane >> 5)] = zs;
   __syncthreads();
@@ -292,134 +379,319 @@ __global__ __launch_bounds__(kFWaves * 64) void k_net_fused(
 
 // da[p][ci] = sum_{tap, co} W[co][ci][tap] dz[p + (1,1) - tap][co], then
 // dzprev = da * silu'(zprev).  CIN = 32 (every layer with an input grad).
+// Bound by memory: 2^20 pixels take 71 us (COUT = 32, 420 B per pixel, 6.1 TB/s)
+// and 59 us (COUT = 2, 330 B); reading dz once per tap instead of once per tile
+// and halo, 65536 pixels took 21 and 10 us.  Held to three wavefronts per SIMD
+// the registers spill (114 us).
 template <int COUT>
 __global__ __launch_bounds__(256) void k_conv_dx(const float* __restrict__ dz,
                                                  const uint16_t* __restrict__ wx,
                                                  const float* __restrict__ zprev,
-                                                 float* __restrict__ dzprev, int H, int W,
-                                                 int lgW) {
-  constexpr int CIN = 32, K = 9 * COUT, KP = pad16(K);
+                                                 float* __restrict__ dzprev, int ntiles, int H,
+                                                 int W, int lgW) {
+  constexpr int CIN = 32, K = 9 * COUT, KP = pad16(K), NKS = KP / 16;
+  constexpr int PS = COUT == 2 ? 2 : kFS;   // LDS pixel stride
+  __shared__ __align__(16) uint16_t in[kHR * kHR * PS];
   const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
-  const int p0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-  const int p = p0 + i;
-  f32x16 acc = {};
-#pragma unroll 2
-  for (int ks = 0; ks < KP / 16; ++ks) {
-    const int k0 = ks * 16 + half * 8;
-    u16x8 av;
-    if constexpr (COUT % 8 == 0) {
-      const int tap = k0 / COUT, co0 = k0 % COUT;
-      const int q = nb(p, 1 - tap / 3, 1 - tap % 3, H, W, lgW);
-      const float4 x0 = *reinterpret_cast<const float4*>(dz + (size_t)q * COUT + co0);
-      const float4 x1 = *reinterpret_cast<const float4*>(dz + (size_t)q * COUT + co0 + 4);
-      av[0] = f2bf(x0.x); av[1] = f2bf(x0.y); av[2] = f2bf(x0.z); av[3] = f2bf(x0.w);
-      av[4] = f2bf(x1.x); av[5] = f2bf(x1.y); av[6] = f2bf(x1.z); av[7] = f2bf(x1.w);
-    } else {
+  u16x8 bv[NKS];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int k = k0 + e;
-        uint16_t v = 0;
-        if (k < K) {
-          const int tap = k / COUT, co = k % COUT;
-          v = f2bf(dz[(size_t)nb(p, 1 - tap / 3, 1 - tap % 3, H, W, lgW) * COUT + co]);
+  for (int ks = 0; ks < NKS; ++ks)
+    bv[ks] = *reinterpret_cast<const u16x8*>(wx + i * KP + ks * 16 + half * 8);
+  for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
+    const TileAt at = tile_at(tile, H, W, lgW);
+    auto pixel = [&](int q) { return halo_px(at, q, H, W, lgW); };
+    if constexpr (COUT == 2) {
+      f32x2_any v[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int q = (int)threadIdx.x + u * 256;
+        if (q < kHR * kHR) v[u] = *reinterpret_cast<const f32x2_any*>(dz + pixel(q) * 2);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int q = (int)threadIdx.x + u * 256;
+        if (q < kHR * kHR)
+          *reinterpret_cast<unsigned*>(in + 2 * q) =
+              (unsigned)f2bf(v[u].x) | ((unsigned)f2bf(v[u].y) << 16);
+      }
+    } else {
+      constexpr int NI = kHR * kHR * 8, NT = (NI + 255) / 256;
+      float4 v[NT];
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int it = (int)threadIdx.x + u * 256;
+        if (it < NI)
+          v[u] = *reinterpret_cast<const float4*>(dz + pixel(it >> 3) * 32 + (it & 7) * 4);
+      }
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int it = (int)threadIdx.x + u * 256;
+        if (it < NI) {
+          const uint2 w = {(unsigned)f2bf(v[u].x) | ((unsigned)f2bf(v[u].y) << 16),
+                           (unsigned)f2bf(v[u].z) | ((unsigned)f2bf(v[u].w) << 16)};
+          *reinterpret_cast<uint2*>(in + (it >> 3) * PS + (it & 7) * 4) = w;
         }
-        av[e] = v;
       }
     }
-    const u16x8 bv = *reinterpret_cast<const u16x8*>(wx + (size_t)i * KP + k0);
-    acc = mfma(av, bv, acc);
-  }
-  const int ci = i;
+    __syncthreads();
+    for (int mt = (int)(threadIdx.x >> 6); mt < kFT * kFT / 32; mt += 4) {
+      const int t = mt * 32 + i;
+      auto elem = [&](int r) { return tile_px(at, mt * 32 + c_row(r, half), lgW) * CIN + i; };
+      float zp[16];
+      if (zprev) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const size_t e = (size_t)(p0 + c_row(r, half)) * CIN + ci;
-    dzprev[e] = zprev ? acc[r] * silu_grad(zprev[e]) : acc[r];
+        for (int r = 0; r < 16; ++r) zp[r] = zprev[elem(r)];
+      }
+      f32x16 acc = {};
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks)
+        acc = mfma(tile_operand<COUT, true>(in, t >> 4, t & 15, ks, half), bv[ks], acc);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) dzprev[elem(r)] = zprev ? acc[r] * silu_grad(zp[r]) : acc[r];
+    }
+    __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------- weight grad
 
-// part[chunk][co][kcol] = sum_{p in chunk} dz[p][co] a[p + tap - (1,1)][ci],
-// kcol = tap CIN + ci.  Block x: a chunk of kDwChunk pixels; each wave one
-// 32-column tile (blockIdx.y * 4 + wave).
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_conv_dw(const float* __restrict__ dz,
-                                                 const uint16_t* __restrict__ a,
-                                                 float* __restrict__ part, int H, int W,
-                                                 int lgW) {
-  constexpr int NK = 9 * CIN, NKT = (NK + 31) / 32, NKP = NKT * 32;
-  const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
-  const int ct = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (ct >= NKT) return;
-  const int chunk = blockIdx.x;
-  const int kcol = ct * 32 + i;
-  const bool colok = kcol < NK;
-  const int tap = colok ? kcol / CIN : 0, ci = colok ? kcol % CIN : 0;
-  const int co = i;
-  f32x16 acc = {};
-  for (int ks = 0; ks < kDwChunk / 16; ++ks) {
-    const int pc = chunk * kDwChunk + ks * 16 + half * 8;
-    u16x8 av, bv;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      av[e] = co < COUT ? f2bf(dz[(size_t)(pc + e) * COUT + co]) : (uint16_t)0;
-      bv[e] = colok ? a[(size_t)nb(pc + e, tap / 3 - 1, tap % 3 - 1, H, W, lgW) * CIN + ci]
-                    : (uint16_t)0;
-    }
-    acc = mfma(av, bv, acc);
-  }
-  if (colok) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = c_row(r, half);
-      if (row < COUT) part[((size_t)chunk * 32 + row) * NKP + kcol] = acc[r];
-    }
-  }
-}
+// part[block] = { dW[co][kcol], db[co] } of the block's tiles, with
+// dW[co][kcol] = sum_p dz[p][co] a[p + tap - (1,1)][ci], kcol = tap CIN + ci,
+// db[co] = sum_p dz[p][co].  Staging transposes both operands to
+// [channel][pixel pair]: eight pixels of a row are then one 16-byte read, and
+// the three taps of a tap row are the same five pairs, shifted by half a pair
+// at a time.  CIN = 32: wavefront w takes tap row w; CIN = 2: one 32-column
+// product covers the 18 columns, and the wavefronts take rows in turn.  The
+// next tile is read into registers while one is multiplied; partials are per
+// block, not per 256 pixels.  Bound by memory (CIN = COUT = 32: 200 B per pixel).
+constexpr int kDwTpb = 192;
+constexpr int kDwRow = 12;                       // dwords per staged row of a (9 pairs)
+constexpr int kDwAs = kHR * kDwRow + 4;          // per channel of a: 28 mod 32 banks
+constexpr int kDwDs = kFT * kFT / 2 + 4;         // per channel of dz: 4 mod 32 banks
 
-// grad[W(co, ci, tap)] += sum over chunks (in order) of part[chunk][co][kcol].
 template <int CIN, int COUT>
-__global__ void k_dw_reduce(const float* __restrict__ part, int nchunk, float* __restrict__ gw) {
-  constexpr int NK = 9 * CIN, NKP = (NK + 31) / 32 * 32;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= COUT * NK) return;
-  const int co = e / NK, kcol = e % NK;
-  float s = 0.f;
-  for (int c = 0; c < nchunk; ++c) s += part[((size_t)c * 32 + co) * NKP + kcol];
-  const int tap = kcol / CIN, ci = kcol % CIN;
-  gw[(co * CIN + ci) * 9 + tap] += s;
-}
+__global__ __launch_bounds__(kDwTpb) void k_conv_dw(const float* __restrict__ dz,
+                                                    const uint16_t* __restrict__ a,
+                                                    float* __restrict__ part, int ntiles, int H,
+                                                    int W, int lgW) {
+  constexpr int NK = 9 * CIN, REC = COUT * NK + COUT;
+  __shared__ __align__(16) unsigned as[CIN * kDwAs];
+  __shared__ __align__(16) unsigned ds[COUT * kDwDs];
+  __shared__ float dbs[kDwTpb * 4];
+  const int tid = (int)threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63, half = lane >> 5, i = lane & 31;
 
-// gb[co] += sum_p dz[p][co] (one block per channel, fixed-order tree).
-__global__ __launch_bounds__(256) void k_db(const float* __restrict__ dz, int P, int cout,
-                                            float* __restrict__ gb) {
-  __shared__ float red[256];
-  const int co = blockIdx.x;
-  float s = 0.f;
-  for (int p = threadIdx.x; p < P; p += 256) s += dz[(size_t)p * cout + co];
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int h = 128; h >= 1; h >>= 1) {
-    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+  constexpr int GA = CIN == 32 ? 4 : 1, NA = kHR * (kHR / 2) * GA, NAT = (NA + kDwTpb - 1) / kDwTpb;
+  constexpr int GD = COUT == 32 ? 8 : 1, ND = kFT * kFT / 2 * GD, NDT = (ND + kDwTpb - 1) / kDwTpb;
+  u16x8 ra[NAT][CIN == 32 ? 2 : 1];
+  f32x4_any rd[NDT][COUT == 32 ? 2 : 1];
+  auto fetch = [&](int tile) {
+    const TileAt at = tile_at(tile, H, W, lgW);
+#pragma unroll
+    for (int u = 0; u < NAT; ++u) {
+      const int it = tid + u * kDwTpb;
+      if (it < NA) {
+        const int pr = it / GA, row = pr / (kHR / 2), j = pr % (kHR / 2);
+        const size_t line = at.base + (size_t)(((at.y0 - 1 + row) & (H - 1)) << lgW);
+        const size_t q0 = line + ((at.x0 - 1 + 2 * j) & (W - 1));
+        const size_t q1 = line + ((at.x0 + 2 * j) & (W - 1));
+        if constexpr (CIN == 32) {
+          ra[u][0] = *reinterpret_cast<const u16x8_any*>(a + q0 * 32 + (it % GA) * 8);
+          ra[u][1] = *reinterpret_cast<const u16x8_any*>(a + q1 * 32 + (it % GA) * 8);
+        } else {
+          const unsigned v0 = *reinterpret_cast<const u32_any*>(a + q0 * 2);
+          const unsigned v1 = *reinterpret_cast<const u32_any*>(a + q1 * 2);
+          ra[u][0][0] = (uint16_t)v0;
+          ra[u][0][1] = (uint16_t)(v0 >> 16);
+          ra[u][0][2] = (uint16_t)v1;
+          ra[u][0][3] = (uint16_t)(v1 >> 16);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NDT; ++u) {
+      const int it = tid + u * kDwTpb;
+      if (it < ND) {
+        const int pr = it / GD, row = pr / (kFT / 2), j = pr % (kFT / 2);
+        const size_t q = at.base + (size_t)(((at.y0 + row) << lgW) + at.x0 + 2 * j);
+        if constexpr (COUT == 32) {
+          rd[u][0] = *reinterpret_cast<const f32x4_any*>(dz + q * 32 + (it % GD) * 4);
+          rd[u][1] = *reinterpret_cast<const f32x4_any*>(dz + q * 32 + 32 + (it % GD) * 4);
+        } else {
+          rd[u][0] = *reinterpret_cast<const f32x4_any*>(dz + q * 2);
+        }
+      }
+    }
+  };
+  float db[4] = {0.f, 0.f, 0.f, 0.f};   // channels 4 (tid % 8) + c, or c
+  auto put = [&] {
+    auto pair = [](uint16_t lo, uint16_t hi) { return (unsigned)lo | ((unsigned)hi << 16); };
+#pragma unroll
+    for (int u = 0; u < NAT; ++u) {
+      const int it = tid + u * kDwTpb;
+      if (it < NA) {
+        const int pr = it / GA;
+        unsigned* o = as + pr / (kHR / 2) * kDwRow + pr % (kHR / 2);
+        if constexpr (CIN == 32) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c)
+            o[((it % GA) * 8 + c) * kDwAs] = pair(ra[u][0][c], ra[u][1][c]);
+        } else {
+          o[0] = pair(ra[u][0][0], ra[u][0][2]);
+          o[kDwAs] = pair(ra[u][0][1], ra[u][0][3]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NDT; ++u) {
+      const int it = tid + u * kDwTpb;
+      if (it < ND) {
+        const int pr = it / GD;
+        if constexpr (COUT == 32) {
+          const f32x4_any x0 = rd[u][0], x1 = rd[u][1];
+          unsigned* o = ds + (it % GD) * 4 * kDwDs + pr;
+          o[0] = pair(f2bf(x0.x), f2bf(x1.x));
+          o[kDwDs] = pair(f2bf(x0.y), f2bf(x1.y));
+          o[2 * kDwDs] = pair(f2bf(x0.z), f2bf(x1.z));
+          o[3 * kDwDs] = pair(f2bf(x0.w), f2bf(x1.w));
+          db[0] += x0.x + x1.x;
+          db[1] += x0.y + x1.y;
+          db[2] += x0.z + x1.z;
+          db[3] += x0.w + x1.w;
+        } else {
+          const f32x4_any x = rd[u][0];
+          ds[pr] = pair(f2bf(x.x), f2bf(x.z));
+          ds[kDwDs + pr] = pair(f2bf(x.y), f2bf(x.w));
+          db[0] += x.x + x.z;
+          db[1] += x.y + x.w;
+        }
+      }
+    }
+  };
+
+  constexpr int NACC = CIN == 32 ? 3 : 1;
+  f32x16 acc[NACC] = {};
+  const int tap = i < NK ? i / 2 : 0, tx = tap % 3;   // CIN = 2: this lane's column
+  fetch((int)blockIdx.x);
+  for (int tile = (int)blockIdx.x; tile < ntiles; tile += (int)gridDim.x) {
+    put();
+    __syncthreads();
+    if (tile + (int)gridDim.x < ntiles) fetch(tile + (int)gridDim.x);
+    for (int ks = CIN == 32 ? 0 : wave; ks < kFT; ks += CIN == 32 ? 1 : 3) {
+      uint4 av = {0u, 0u, 0u, 0u};
+      if (i < COUT)
+        av = *reinterpret_cast<const uint4*>(ds + i * kDwDs + ks * (kFT / 2) + 4 * half);
+      const u16x8 A = __builtin_bit_cast(u16x8, av);
+      auto shifted = [](uint4 p, unsigned p4, unsigned by) {
+        const uint4 v = {
+            __builtin_amdgcn_alignbit(p.y, p.x, by), __builtin_amdgcn_alignbit(p.z, p.y, by),
+            __builtin_amdgcn_alignbit(p.w, p.z, by), __builtin_amdgcn_alignbit(p4, p.w, by)};
+        return __builtin_bit_cast(u16x8, v);
+      };
+      if constexpr (CIN == 32) {
+        const unsigned* b = as + i * kDwAs + (ks + wave) * kDwRow + 4 * half;
+        const uint4 p = *reinterpret_cast<const uint4*>(b);
+        const unsigned p4 = b[4];
+        const uint4 p1 = {p.y, p.z, p.w, p4};
+        acc[0] = mfma(A, __builtin_bit_cast(u16x8, p), acc[0]);
+        acc[1] = mfma(A, shifted(p, p4, 16), acc[1]);
+        acc[2] = mfma(A, __builtin_bit_cast(u16x8, p1), acc[2]);
+      } else {
+        const unsigned* b = as + (i & 1) * kDwAs + (ks + tap / 3) * kDwRow + 4 * half + (tx == 2);
+        const uint4 p = {b[0], b[1], b[2], b[3]};
+        const u16x8 B = shifted(p, b[4], tx == 1 ? 16u : 0u);
+        acc[0] = mfma(A, i < NK ? B : u16x8{}, acc[0]);
+      }
+    }
     __syncthreads();
   }
-  if (threadIdx.x == 0) gb[co] += red[0];
+
+  float* out = part + (size_t)blockIdx.x * REC;
+  if constexpr (CIN == 32) {
+#pragma unroll
+    for (int x = 0; x < 3; ++x)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int row = c_row(r, half);
+        if (row < COUT) out[row * NK + (wave * 3 + x) * 32 + i] = acc[x][r];
+      }
+  } else {
+    static_assert(CIN == 32 || COUT * kDwDs >= 3 * 32 * 32, "the three wavefronts' sums");
+    float* red = reinterpret_cast<float*>(ds);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[(wave * 32 + c_row(r, half)) * 32 + i] = acc[0][r];
+    __syncthreads();
+    for (int e = tid; e < COUT * NK; e += kDwTpb) {
+      const int row = e / NK, col = e % NK;
+      out[e] = red[row * 32 + col] + red[(32 + row) * 32 + col] + red[(64 + row) * 32 + col];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) dbs[tid * 4 + c] = db[c];
+  __syncthreads();
+  if (tid < COUT) {
+    double s = 0.0;
+    for (int t = COUT == 32 ? tid / 4 : 0; t < kDwTpb; t += GD) s += (double)dbs[t * 4 + tid % 4];
+    out[COUT * NK + tid] = (float)s;
+  }
+}
+
+struct GradParts {
+  const float* part[kCnnLayers];   // nb[l] records { dW, db } of layer l
+  int nb[kCnnLayers];
+};
+
+// grad[e] += the sum of the partials of parameter e, e0 <= e < e1.  64
+// parameters per block, their records over 16 wavefronts (fixed order, FP64).
+__global__ __launch_bounds__(1024) void k_grad_reduce(GradParts parts, float* __restrict__ grad,
+                                                      int e0, int e1) {
+  __shared__ double red[16][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int e = e0 + (int)blockIdx.x * 64 + lane;
+  const int l = e >= kOffW[3] ? 3 : e >= kOffW[2] ? 2 : e >= kOffW[1] ? 1 : 0;
+  const int cin = l ? 32 : 2, cout = l < 3 ? 32 : 2, nk = 9 * cin, rec = cout * (nk + 1);
+  const int off = l == 3 ? kOffW[3] : l == 2 ? kOffW[2] : l == 1 ? kOffW[1] : kOffW[0];
+  const float* part = l == 3   ? parts.part[3]
+                      : l == 2 ? parts.part[2]
+                      : l == 1 ? parts.part[1]
+                               : parts.part[0];
+  const int nb = l == 3 ? parts.nb[3] : l == 2 ? parts.nb[2] : l == 1 ? parts.nb[1] : parts.nb[0];
+  double s = 0.0;
+  if (e < e1) {
+    const float* p = part + (e - off);
+#pragma unroll 8
+    for (int b = w; b < nb; b += 16) s += (double)p[(size_t)b * rec];
+  }
+  red[w][lane] = s;
+  __syncthreads();
+  if (w == 0 && e < e1) {
+    for (int k = 1; k < 16; ++k) s += red[k][lane];
+    int d = e - off;
+    if (d < cout * nk) {
+      const int co = d / nk, kcol = d % nk;
+      d = (co * cin + kcol % cin) * 9 + kcol / cin;
+    }
+    grad[off + d] += (float)s;
+  }
 }
 
 // ---------------------------------------------------------------- loss, I/O
 
 // r = z4 * s_out; e = r - t; dz4 = scale * e * s_out; per-block sum of e^2.
+// n pixels over samples of P = 2^lgP (t: two planes per sample).
 __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z4,
-                                              const float* __restrict__ t, int P, float s2,
-                                              float s3, float scale, float* __restrict__ dz4,
+                                              const float* __restrict__ t, int n, int lgP,
+                                              float s2, float s3, float scale,
+                                              float* __restrict__ dz4,
                                               double* __restrict__ part) {
   __shared__ double red[256];
   double acc = 0.0;
-  for (int p = blockIdx.x * 256 + threadIdx.x; p < P; p += gridDim.x * 256) {
-    const float e0 = z4[2 * (size_t)p] * s2 - t[p];
-    const float e1 = z4[2 * (size_t)p + 1] * s3 - t[(size_t)P + p];
-    dz4[2 * (size_t)p] = scale * e0 * s2;
-    dz4[2 * (size_t)p + 1] = scale * e1 * s3;
+  for (int p = blockIdx.x * 256 + threadIdx.x; p < n; p += gridDim.x * 256) {
+    const float* tp = t + p + ((size_t)(p >> lgP) << lgP);
+    const float2 z = *reinterpret_cast<const float2*>(z4 + 2 * (size_t)p);
+    const float e0 = z.x * s2 - tp[0];
+    const float e1 = z.y * s3 - tp[(size_t)1 << lgP];
+    *reinterpret_cast<float2*>(dz4 + 2 * (size_t)p) = {scale * e0 * s2, scale * e1 * s3};
     acc += (double)e0 * e0 + (double)e1 * e1;
   }
   red[threadIdx.x] = acc;
@@ -431,8 +703,7 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z4,
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// out[slot] += sum of n partials (one thread, fixed order).
-// out[0] (+)= sum of part[0 .. n), n <= 1024, as one block's fixed-order
+// out[0] (+)= sum of part[0 .. n) as one block's fixed-order
 // tree; acc = 0 overwrites (no clearing launch needed, so the call may sit
 // in a captured graph).  Launch with 256 threads.
 __global__ __launch_bounds__(256) void k_sum_into(const double* __restrict__ part, int n,
@@ -449,12 +720,13 @@ __global__ __launch_bounds__(256) void k_sum_into(const double* __restrict__ par
   if (threadIdx.x == 0) out[0] = (acc ? out[0] : 0.0) + red[0];
 }
 
-template <typename T>
-__global__ void k_pack_input(const T* __restrict__ x0, const T* __restrict__ x1, int P,
-                             float s0, float s1, uint16_t* __restrict__ a0) {
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < P; p += gridDim.x * blockDim.x) {
-    a0[2 * (size_t)p] = f2bf((float)x0[p] * s0);
-    a0[2 * (size_t)p + 1] = f2bf((float)x1[p] * s1);
+// Layer 0's input of n pixels over samples of P = 2^lgP (x: two planes each).
+__global__ void k_pack_input(const float* __restrict__ x, int n, int lgP, float s0, float s1,
+                             uint16_t* __restrict__ a0) {
+  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < n; p += gridDim.x * blockDim.x) {
+    const float* xp = x + p + ((size_t)(p >> lgP) << lgP);
+    reinterpret_cast<unsigned*>(a0)[p] =
+        (unsigned)f2bf(xp[0] * s0) | ((unsigned)f2bf(xp[(size_t)1 << lgP] * s1) << 16);
   }
 }
 
@@ -529,63 +801,70 @@ __global__ void k_mfma_probe(const uint16_t* __restrict__ a, const uint16_t* __r
 
 int alloc_dev(void** p, size_t bytes) { return hipMalloc(p, bytes) == hipSuccess ? 0 : -2; }
 
-void launch_fwd(const Net* n, int li, const uint16_t* a_in, float* z, uint16_t* a_out,
-                hipStream_t st) {
-  const dim3 g(n->P / 128), b(256);
-  switch (li) {
-    case 0:
-      hipLaunchKernelGGL((k_conv_fwd<2, 32, true>), g, b, 0, st, a_in, n->wt[0],
-                         n->params + kOffB[0], z, a_out, n->H, n->W, n->lgW);
-      break;
-    case 1:
-      hipLaunchKernelGGL((k_conv_fwd<32, 32, true>), g, b, 0, st, a_in, n->wt[1],
-                         n->params + kOffB[1], z, a_out, n->H, n->W, n->lgW);
-      break;
-    case 2:
-      hipLaunchKernelGGL((k_conv_fwd<32, 32, true>), g, b, 0, st, a_in, n->wt[2],
-                         n->params + kOffB[2], z, a_out, n->H, n->W, n->lgW);
-      break;
-    default:
-      hipLaunchKernelGGL((k_conv_fwd<32, 2, false>), g, b, 0, st, a_in, n->wt[3],
-                         n->params + kOffB[3], z, a_out, n->H, n->W, n->lgW);
-      break;
+// The pixel kernels' grid over n pixels (four blocks per CU at most).
+int px_blocks(int n) { return n / 256 < 1024 ? n / 256 : 1024; }
+
+void launch_fwd(const Net* n, int li, int samples, const uint16_t* a_in, float* z,
+                uint16_t* a_out, hipStream_t st) {
+  const int nt = samples * (n->P / (kFT * kFT));
+  const int cap = li ? kFwdBlocks : kConvBlocks;
+  const dim3 g(nt < cap ? nt : cap), b(256);
+  const float* bias = n->params + kOffB[li];
+  if (li == 0)
+    hipLaunchKernelGGL((k_conv_fwd<2, 32, true>), g, b, 0, st, a_in, n->wt[0], bias, z, a_out, nt,
+                       n->H, n->W, n->lgW);
+  else if (li < 3)
+    hipLaunchKernelGGL((k_conv_fwd<32, 32, true>), g, b, 0, st, a_in, n->wt[li], bias, z, a_out,
+                       nt, n->H, n->W, n->lgW);
+  else
+    hipLaunchKernelGGL((k_conv_fwd<32, 2, false>), g, b, 0, st, a_in, n->wt[3], bias, z, a_out,
+                       nt, n->H, n->W, n->lgW);
+}
+
+// The weight gradient's partials: layer l's dw_blocks(l) records at
+// part + dw_part(l).
+int dw_blocks(int li, int ntiles) { return ntiles < kDwBlocks[li] ? ntiles : kDwBlocks[li]; }
+int dw_rec(int li) { return kOffB[li] + kCnnCout[li] - kOffW[li]; }
+size_t dw_part(int li) {
+  size_t o = 0;
+  for (int l = 0; l < li; ++l) o += (size_t)kDwBlocks[l] * dw_rec(l);
+  return o;
+}
+
+// Weight and bias gradient partials of layer li over `samples` samples; the
+// input gradient (times silu' of zprev, when given) into dzprev for li > 0.
+void launch_bwd(const Net* n, int li, int samples, const float* dz, const uint16_t* a_in,
+                const float* zprev, float* dzprev, hipStream_t st) {
+  const int nt = samples * (n->P / (kFT * kFT)), nb = dw_blocks(li, nt);
+  const dim3 b(kDwTpb), g(nb);
+  float* part = n->part + dw_part(li);
+  if (li == 0)
+    hipLaunchKernelGGL((k_conv_dw<2, 32>), g, b, 0, st, dz, a_in, part, nt, n->H, n->W, n->lgW);
+  else if (li < 3)
+    hipLaunchKernelGGL((k_conv_dw<32, 32>), g, b, 0, st, dz, a_in, part, nt, n->H, n->W, n->lgW);
+  else
+    hipLaunchKernelGGL((k_conv_dw<32, 2>), g, b, 0, st, dz, a_in, part, nt, n->H, n->W, n->lgW);
+  if (li > 0 && dzprev) {
+    const dim3 gx(nt < kConvBlocks ? nt : kConvBlocks);
+    if (li < 3)
+      hipLaunchKernelGGL((k_conv_dx<32>), gx, dim3(256), 0, st, dz, n->wx[li], zprev, dzprev, nt,
+                         n->H, n->W, n->lgW);
+    else
+      hipLaunchKernelGGL((k_conv_dx<2>), gx, dim3(256), 0, st, dz, n->wx[li], zprev, dzprev, nt,
+                         n->H, n->W, n->lgW);
   }
 }
 
-// Weight and bias gradients of layer li accumulated into n->grad; the input
-// gradient (times silu' of zprev, when given) into dzprev for li > 0.
-void launch_bwd(const Net* n, int li, const float* dz, const uint16_t* a_in, const float* zprev,
-                float* dzprev, hipStream_t st) {
-  const int nchunk = n->P / kDwChunk;
-  const dim3 b(256);
-  float* gw = n->grad + kOffW[li];
-  float* gb = n->grad + kOffB[li];
-  if (li == 0) {
-    hipLaunchKernelGGL((k_conv_dw<2, 32>), dim3(nchunk, 1), b, 0, st, dz, a_in, n->part, n->H,
-                       n->W, n->lgW);
-    hipLaunchKernelGGL((k_dw_reduce<2, 32>), dim3((32 * 18 + 255) / 256), b, 0, st, n->part,
-                       nchunk, gw);
-  } else if (li < 3) {
-    hipLaunchKernelGGL((k_conv_dw<32, 32>), dim3(nchunk, 3), b, 0, st, dz, a_in, n->part, n->H,
-                       n->W, n->lgW);
-    hipLaunchKernelGGL((k_dw_reduce<32, 32>), dim3((32 * 288 + 255) / 256), b, 0, st, n->part,
-                       nchunk, gw);
-  } else {
-    hipLaunchKernelGGL((k_conv_dw<32, 2>), dim3(nchunk, 3), b, 0, st, dz, a_in, n->part, n->H,
-                       n->W, n->lgW);
-    hipLaunchKernelGGL((k_dw_reduce<32, 2>), dim3((2 * 288 + 255) / 256), b, 0, st, n->part,
-                       nchunk, gw);
+// The gradient of layers l0 .. l1 += the partials of launch_bwd.
+void launch_reduce(const Net* n, int samples, int l0, int l1, hipStream_t st) {
+  GradParts p;
+  for (int l = 0; l < kCnnLayers; ++l) {
+    p.part[l] = n->part + dw_part(l);
+    p.nb[l] = dw_blocks(l, samples * (n->P / (kFT * kFT)));
   }
-  hipLaunchKernelGGL(k_db, dim3(kCnnCout[li]), b, 0, st, dz, n->P, kCnnCout[li], gb);
-  if (li > 0 && dzprev) {
-    const dim3 g(n->P / 128);
-    if (li < 3)
-      hipLaunchKernelGGL((k_conv_dx<32>), g, b, 0, st, dz, n->wx[li], zprev, dzprev, n->H, n->W,
-                         n->lgW);
-    else
-      hipLaunchKernelGGL((k_conv_dx<2>), g, b, 0, st, dz, n->wx[li], zprev, dzprev, n->H, n->W,
-                         n->lgW);
-  }
+  const int e0 = kOffW[l0], e1 = kOffB[l1] + kCnnCout[l1];
+  hipLaunchKernelGGL(k_grad_reduce, dim3((e1 - e0 + 63) / 64), dim3(1024), 0, st, p, n->grad, e0,
+                     e1);
 }
 
 void launch_pack_weights(Net* n, hipStream_t st) {
@@ -595,13 +874,51 @@ void launch_pack_weights(Net* n, hipStream_t st) {
 
 }  // namespace
 
+// Buffers of `samples` samples at once for the training step.
+int train_alloc(TrainWork* w, int P, int samples) {
+  const size_t px = (size_t)P * samples;
+  int rc = 0;
+  for (int l = 0; l < kCnnLayers; ++l)
+    rc = rc ? rc : alloc_dev((void**)&w->act[l], px * kCnnCin[l] * 2);
+  for (int l = 0; l < kCnnLayers; ++l)
+    rc = rc ? rc : alloc_dev((void**)&w->z[l], px * kCnnCout[l] * sizeof(float));
+  for (int k = 0; k < 2; ++k) rc = rc ? rc : alloc_dev((void**)&w->dz[k], px * 32 * sizeof(float));
+  if (!rc) w->samples = samples;
+  return rc;
+}
+
+void train_free(TrainWork* w) {
+  void* ps[] = {w->act[0], w->act[1], w->act[2], w->act[3], w->z[0],
+                w->z[1],   w->z[2],   w->z[3],   w->dz[0],  w->dz[1]};
+  for (void* p : ps)
+    if (p) (void)hipFree(p);
+  *w = TrainWork();
+}
+
+// Room for B samples at once, at most kGroupPixels pixels; with less memory
+// than that, for as many as fit (one at least).
+int train_reserve(Net* n, int B) {
+  int want = kGroupPixels / n->P;
+  want = want < 1 ? 1 : want > B ? B : want;
+  if (n->work.samples >= want) return 0;
+  train_free(&n->work);
+  for (; want >= 1; want /= 2) {
+    if (!train_alloc(&n->work, n->P, want)) return 0;
+    train_free(&n->work);
+    (void)hipGetLastError();
+  }
+  return -2;
+}
+
 int net_create(Net* n, int H, int W, bool training) {
-  if (H < 16 || W < 16 || (H & (H - 1)) || (W & (W - 1)) || (size_t)H * W % kDwChunk) return -1;
+  if (H < 16 || W < 16 || (H & (H - 1)) || (W & (W - 1))) return -1;
   n->H = H;
   n->W = W;
   n->lgW = 0;
   while ((1 << n->lgW) < W) ++n->lgW;
   n->P = H * W;
+  n->lgP = n->lgW;
+  while ((1 << n->lgP) < n->P) ++n->lgP;
   const size_t P = (size_t)n->P;
   int rc = 0;
   rc = rc ? rc : alloc_dev((void**)&n->params, kCnnParams * sizeof(float));
@@ -611,17 +928,15 @@ int net_create(Net* n, int H, int W, bool training) {
     rc = rc ? rc : alloc_dev((void**)&n->act[l], P * kCnnCin[l] * 2);
     rc = rc ? rc : alloc_dev((void**)&n->z[l], P * kCnnCout[l] * sizeof(float));
   }
-  // reduction scratch: the corrected step's P/256 per-tile partials; the
-  // loss's 256 partials and its running sum at [1024]
-  const size_t nred = (P / 256 > 2048 ? P / 256 : 2048);
+  // the corrected step's per-tile partials; the loss and its partials
+  const size_t nred = P / (kFT * kFT) > 1025 ? P / (kFT * kFT) : 1025;
   rc = rc ? rc : alloc_dev((void**)&n->red, nred * sizeof(double));
   if (training) {
     rc = rc ? rc : alloc_dev((void**)&n->grad, kCnnParams * sizeof(float));
     rc = rc ? rc : alloc_dev((void**)&n->m, kCnnParams * sizeof(float));
     rc = rc ? rc : alloc_dev((void**)&n->v, kCnnParams * sizeof(float));
-    rc = rc ? rc : alloc_dev((void**)&n->dz[0], P * 32 * sizeof(float));
-    rc = rc ? rc : alloc_dev((void**)&n->dz[1], P * 32 * sizeof(float));
-    rc = rc ? rc : alloc_dev((void**)&n->part, (P / kDwChunk) * 32 * 288 * sizeof(float));
+    rc = rc ? rc : alloc_dev((void**)&n->part, dw_part(kCnnLayers) * sizeof(float));
+    rc = rc ? rc : train_reserve(n, 1);
     if (!rc && (hipMemset(n->grad, 0, kCnnParams * 4) || hipMemset(n->m, 0, kCnnParams * 4) ||
                 hipMemset(n->v, 0, kCnnParams * 4)))
       rc = -3;
@@ -631,9 +946,10 @@ int net_create(Net* n, int H, int W, bool training) {
 }
 
 void net_destroy(Net* n) {
-  void* ps[] = {n->params, n->grad, n->m, n->v, n->dz[0], n->dz[1], n->part, n->red};
+  void* ps[] = {n->params, n->grad, n->m, n->v, n->part, n->red};
   for (void* p : ps)
     if (p) (void)hipFree(p);
+  train_free(&n->work);
   for (int l = 0; l < kCnnLayers; ++l) {
     if (n->wt[l]) (void)hipFree(n->wt[l]);
     if (n->wx[l]) (void)hipFree(n->wx[l]);
@@ -653,10 +969,10 @@ int net_set_params(Net* n, const float* host, hipStream_t st) {
 
 int net_forward_planes(Net* n, const float* x, float* r, hipStream_t st) {
   const int P = n->P;
-  hipLaunchKernelGGL((k_pack_input<float>), dim3(256), dim3(256), 0, st, x, x + P, P,
+  hipLaunchKernelGGL(k_pack_input, dim3(px_blocks(P)), dim3(256), 0, st, x, P, n->lgP,
                      n->scales[0], n->scales[1], n->act[0]);
   for (int l = 0; l < kCnnLayers; ++l)
-    launch_fwd(n, l, n->act[l], n->z[l], l < 3 ? n->act[l + 1] : nullptr, st);
+    launch_fwd(n, l, 1, n->act[l], n->z[l], l < 3 ? n->act[l + 1] : nullptr, st);
   hipLaunchKernelGGL(k_unpack_out, dim3(256), dim3(256), 0, st, n->z[3], P, n->scales[2],
                      n->scales[3], r);
   CNN_TRY(hipGetLastError());
@@ -664,30 +980,30 @@ int net_forward_planes(Net* n, const float* x, float* r, hipStream_t st) {
 }
 
 int net_grad(Net* n, const float* xs, const float* ts, int B, double* loss, hipStream_t st) {
-  if (!n->grad || B < 1) return -1;
+  if (!n->grad || B < 1 || train_reserve(n, B)) return -1;
   const int P = n->P;
   const float scale = 2.0f / ((float)B * 2.0f * (float)P);
-  CNN_TRY(hipMemsetAsync(n->red + 1024, 0, sizeof(double), st));
-  for (int s = 0; s < B; ++s) {
-    const float* x = xs + (size_t)s * 2 * P;
-    const float* t = ts + (size_t)s * 2 * P;
-    hipLaunchKernelGGL((k_pack_input<float>), dim3(256), dim3(256), 0, st, x, x + P, P,
-                       n->scales[0], n->scales[1], n->act[0]);
+  const TrainWork& w = n->work;
+  for (int s = 0; s < B; s += w.samples) {
+    const int ns = B - s < w.samples ? B - s : w.samples, px = ns * P, nbl = px_blocks(px);
+    hipLaunchKernelGGL(k_pack_input, dim3(nbl), dim3(256), 0, st, xs + (size_t)s * 2 * P, px,
+                       n->lgP, n->scales[0], n->scales[1], w.act[0]);
     for (int l = 0; l < kCnnLayers; ++l)
-      launch_fwd(n, l, n->act[l], n->z[l], l < 3 ? n->act[l + 1] : nullptr, st);
-    hipLaunchKernelGGL(k_loss, dim3(256), dim3(256), 0, st, n->z[3], t, P, n->scales[2],
-                       n->scales[3], scale, n->dz[0], n->red);
-    hipLaunchKernelGGL(k_sum_into, dim3(1), dim3(256), 0, st, n->red, 256, n->red + 1024, 1);
+      launch_fwd(n, l, ns, w.act[l], w.z[l], l < 3 ? w.act[l + 1] : nullptr, st);
+    hipLaunchKernelGGL(k_loss, dim3(nbl), dim3(256), 0, st, w.z[3], ts + (size_t)s * 2 * P, px,
+                       n->lgP, n->scales[2], n->scales[3], scale, w.dz[0], n->red + 1);
+    hipLaunchKernelGGL(k_sum_into, dim3(1), dim3(256), 0, st, n->red + 1, nbl, n->red, s > 0);
     int cur = 0;
     for (int l = kCnnLayers - 1; l >= 0; --l) {
-      launch_bwd(n, l, n->dz[cur], n->act[l], l > 0 ? n->z[l - 1] : nullptr,
-                 l > 0 ? n->dz[cur ^ 1] : nullptr, st);
+      launch_bwd(n, l, ns, w.dz[cur], w.act[l], l > 0 ? w.z[l - 1] : nullptr,
+                 l > 0 ? w.dz[cur ^ 1] : nullptr, st);
       cur ^= 1;
     }
+    launch_reduce(n, ns, 0, kCnnLayers - 1, st);
   }
   CNN_TRY(hipGetLastError());
   double h = 0.0;
-  CNN_TRY(hipMemcpyAsync(&h, n->red + 1024, sizeof(double), hipMemcpyDeviceToHost, st));
+  CNN_TRY(hipMemcpyAsync(&h, n->red, sizeof(double), hipMemcpyDeviceToHost, st));
   CNN_TRY(hipStreamSynchronize(st));
   if (loss) *loss = h / ((double)B * 2.0 * P);
   return 0;
@@ -708,7 +1024,7 @@ int net_adam(Net* n, float lr, float b1, float b2, float eps, hipStream_t st) {
 int net_layer_fwd(Net* n, int li, const uint16_t* a_in, float* z_out, uint16_t* a_out,
                   hipStream_t st) {
   if (li < 0 || li >= kCnnLayers) return -1;
-  launch_fwd(n, li, a_in, z_out, li < 3 ? a_out : nullptr, st);
+  launch_fwd(n, li, 1, a_in, z_out, li < 3 ? a_out : nullptr, st);
   CNN_TRY(hipGetLastError());
   return 0;
 }
@@ -717,7 +1033,8 @@ int net_layer_bwd(Net* n, int li, const float* dz, const uint16_t* a_in, const f
                   float* dzprev, float* dw, hipStream_t st) {
   if (li < 0 || li >= kCnnLayers || !n->grad) return -1;
   CNN_TRY(hipMemsetAsync(n->grad, 0, kCnnParams * sizeof(float), st));
-  launch_bwd(n, li, dz, a_in, zprev, dzprev, st);
+  launch_bwd(n, li, 1, dz, a_in, zprev, dzprev, st);
+  launch_reduce(n, 1, li, li, st);
   CNN_TRY(hipGetLastError());
   if (dw) {
     const int len = kOffB[li] + kCnnCout[li] - kOffW[li];

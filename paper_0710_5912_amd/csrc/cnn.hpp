@@ -7,8 +7,8 @@
 // (v_mfma_f32_32x32x16_bf16, FP32 accumulation):
 //   forward       M = pixels, N = Cout, K = 9 Cin
 //   input grad    M = pixels, N = Cin,  K = 9 Cout
-//   weight grad   M = Cout,   N = 9 Cin, K = pixels (split over pixel chunks,
-//                 chunks summed in a fixed order)
+//   weight grad   M = Cout,   N = 9 Cin, K = pixels (split over blocks, whose
+//                 sums are added in a fixed order)
 // Master weights are FP32; the MFMA operands are BF16 copies repacked after
 // every optimiser step.
 #pragma once
@@ -22,12 +22,20 @@ constexpr int kCnnLayers = 4;
 constexpr int kCnnCin[kCnnLayers] = {2, 32, 32, 32};
 constexpr int kCnnCout[kCnnLayers] = {32, 32, 32, 2};
 constexpr int kCnnParams = 2 * 32 * 9 + 32 + 32 * 32 * 9 + 32 + 32 * 32 * 9 + 32 + 32 * 2 * 9 + 2;
-constexpr int kDwChunk = 256;   // pixels per weight-gradient partial
 
-// Network state on one device (weights and, when training, optimiser state
-// and per-sample buffers for a grid of H x W pixels).
+// What a training step keeps of `samples` samples at once (grown to the batch
+// on first use, at most 2^20 pixels).
+struct TrainWork {
+  int samples = 0;
+  uint16_t* act[kCnnLayers] = {};  // inputs of each layer, BF16 [px][Cin]
+  float* z[kCnnLayers] = {};       // pre-activations FP32 [px][Cout]
+  float* dz[2] = {};               // gradient ping-pong FP32 [px][32]
+};
+
+// Network state on one device (weights, one sample's buffers for a grid of
+// H x W pixels and, when training, optimiser state and the step's workspace).
 struct Net {
-  int H = 0, W = 0, lgW = 0, P = 0;
+  int H = 0, W = 0, P = 0, lgW = 0, lgP = 0;   // P = H W pixels
   float* params = nullptr;      // FP32 master, kCnnParams
   float* grad = nullptr;        // FP32, kCnnParams
   float* m = nullptr;           // Adam moments
@@ -37,8 +45,8 @@ struct Net {
   float scales[4] = {1.f, 1.f, 1.f, 1.f};   // in_phi, in_omega, out_phi, out_omega
   uint16_t* act[kCnnLayers] = {};  // inputs of each layer, BF16 [P][Cin]
   float* z[kCnnLayers] = {};       // pre-activations FP32 [P][Cout]
-  float* dz[2] = {};               // gradient ping-pong FP32 [P][32]
   float* part = nullptr;           // weight-gradient partials
+  TrainWork work;
   double* red = nullptr;           // reduction scratch (FP64)
   int64_t adam_t = 0;
 };
