@@ -13,12 +13,14 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "../../include/le.h"
@@ -209,7 +211,11 @@ struct le_ctx {
   double* d_out = nullptr;
   double* h_out = nullptr;
   int nsblk_max = 0, nbins_max = 0;
-  void* h_stage = nullptr;       // pinned staging, largest run
+  void* h_stage = nullptr;       // pinned staging, largest run (three fields of
+                                 // it up to kStageAll values)
+  static constexpr size_t kStageAll = (size_t)1 << 18;
+  static constexpr int kSegs = 4;
+  hipEvent_t seg_ev[kSegs] = {};  // download_real's segments
   size_t stage_bytes = 0;
   bool use_graphs = true;
   std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
@@ -290,12 +296,14 @@ void release(Engine* e) {
     if (r.twy) (void)hipFree(r.twy);
   }
   void* dev[] = {e->d_desc,   e->d_args,   e->d_spart, e->d_rpart,
-                 e->d_bins,   e->d_counts, e->d_gsum,  e->d_out};
+                 e->d_bins,   e->d_counts, e->d_gsum};
   for (void* d : dev)
     if (d) (void)hipFree(d);
   if (e->h_args) (void)hipHostFree(e->h_args);
   if (e->h_out) (void)hipHostFree(e->h_out);
   if (e->h_stage) (void)hipHostFree(e->h_stage);
+  for (hipEvent_t ev : e->seg_ev)
+    if (ev) (void)hipEventDestroy(ev);
   if (e->net) {
     net_destroy(e->net);
     delete e->net;
@@ -322,29 +330,101 @@ int alloc(void** p, size_t bytes) {
   return hipMalloc(p, bytes) == hipSuccess ? LE_OK : LE_ENOMEM;
 }
 
-int upload_real(Engine* e, const RunHost& r, const double* src, int b) {
-  if (r.tsize == sizeof(double)) {
-    std::memcpy(e->h_stage, src, r.n_real * sizeof(double));
-  } else {
-    float* s = static_cast<float*>(e->h_stage);
-    for (size_t i = 0; i < r.n_real; ++i) s[i] = (float)src[i];
+// Host copies of a field run on one thread per 2^17 values, at most 8: a new
+// array's pages are cleared on first touch (4096^2, a state read back after 250
+// FP64 steps: 239 -> 214 ms with the steps, after 100 FP32 steps 100 -> 80).
+constexpr size_t kCopySlice = (size_t)1 << 17;
+constexpr int kCopyThreads = 8;
+int copy_threads(size_t n) {
+  const size_t hw = std::max(1u, std::thread::hardware_concurrency());
+  return (int)std::max<size_t>(1, std::min({n / kCopySlice, hw, (size_t)kCopyThreads}));
+}
+// f(0) .. f(n - 1), each but the first on a thread of its own (or, where none
+// can be started, on this one after f(0)).
+template <typename F>
+void run_threads(int n, F&& f) {
+  std::thread th[kCopyThreads];
+  int k = 1;
+  try {
+    for (; k < n; ++k) th[k] = std::thread([&f, k] { f(k); });
+  } catch (...) {
   }
+  f(0);
+  for (int i = k; i < n; ++i) f(i);
+  for (int i = 1; i < k; ++i) th[i].join();
+}
+
+int upload_real(Engine* e, const RunHost& r, const double* src, int b) {
+  const int nt = copy_threads(r.n_real);
+  run_threads(nt, [&](int t) {
+    const size_t i0 = r.n_real * t / nt, i1 = r.n_real * (t + 1) / nt;
+    if (r.tsize == sizeof(double)) {
+      std::memcpy(static_cast<double*>(e->h_stage) + i0, src + i0, (i1 - i0) * sizeof(double));
+    } else {
+      float* s = static_cast<float*>(e->h_stage);
+      for (size_t i = i0; i < i1; ++i) s[i] = (float)src[i];
+    }
+  });
   LE_TRY(hipMemcpyAsync(r.buf[b], e->h_stage, r.n_real * r.tsize, hipMemcpyHostToDevice,
                         e->stream));
   LE_TRY(hipStreamSynchronize(e->stream));
   return LE_OK;
 }
 
-int download_real(Engine* e, const RunHost& r, int b, double* dst) {
-  LE_TRY(hipMemcpyAsync(e->h_stage, r.buf[b], r.n_real * r.tsize, hipMemcpyDeviceToHost,
-                        e->stream));
-  LE_TRY(hipStreamSynchronize(e->stream));
+// dst[i0 .. i1) from staged values of storage size tsize.
+void widen(const RunHost& r, const void* stage, size_t i0, size_t i1, double* dst) {
   if (r.tsize == sizeof(double)) {
-    std::memcpy(dst, e->h_stage, r.n_real * sizeof(double));
+    std::memcpy(dst + i0, static_cast<const double*>(stage) + i0, (i1 - i0) * sizeof(double));
   } else {
-    const float* s = static_cast<const float*>(e->h_stage);
-    for (size_t i = 0; i < r.n_real; ++i) dst[i] = (double)s[i];
+    const float* s = static_cast<const float*>(stage);
+    for (size_t i = i0; i < i1; ++i) dst[i] = (double)s[i];
   }
+}
+
+// Large fields come over in kSegs segments, each widened by every thread as
+// soon as it is there.
+int download_real(Engine* e, const RunHost& r, int b, double* dst) {
+  const int nt = copy_threads(r.n_real);
+  if (nt == 1) {
+    LE_TRY(hipMemcpyAsync(e->h_stage, r.buf[b], r.n_real * r.tsize, hipMemcpyDeviceToHost,
+                          e->stream));
+    LE_TRY(hipStreamSynchronize(e->stream));
+    widen(r, e->h_stage, 0, r.n_real, dst);
+    return LE_OK;
+  }
+  constexpr int kSegs = Engine::kSegs;
+  for (hipEvent_t& ev : e->seg_ev)
+    if (!ev) LE_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+  auto cut = [&](int s) { return r.n_real * s / kSegs; };
+  hipError_t err = hipSuccess;
+  for (int s = 0; s < kSegs && err == hipSuccess; ++s) {
+    const size_t o = cut(s) * r.tsize, n = cut(s + 1) * r.tsize - o;
+    err = hipMemcpyAsync(static_cast<char*>(e->h_stage) + o, static_cast<char*>(r.buf[b]) + o, n,
+                         hipMemcpyDeviceToHost, e->stream);
+    if (err == hipSuccess) err = hipEventRecord(e->seg_ev[s], e->stream);
+  }
+  LE_TRY(err);
+  std::mutex m;
+  std::condition_variable cv;
+  int ready = 0;   // segments on the host; -1 after an error
+  run_threads(nt, [&](int t) {
+    for (int s = 0; s < kSegs; ++s) {
+      if (t == 0) {
+        err = hipEventSynchronize(e->seg_ev[s]);
+        std::lock_guard<std::mutex> lock(m);
+        ready = err == hipSuccess ? s + 1 : -1;
+        cv.notify_all();
+      }
+      {
+        std::unique_lock<std::mutex> lock(m);
+        cv.wait(lock, [&] { return ready < 0 || ready > s; });
+        if (ready < 0) return;
+      }
+      const size_t i0 = cut(s), n = cut(s + 1) - i0;
+      widen(r, e->h_stage, i0 + n * t / nt, i0 + n * (t + 1) / nt, dst);
+    }
+  });
+  LE_TRY(err);
   return LE_OK;
 }
 
@@ -620,9 +700,6 @@ int reduce_observables(Engine* e, const RunHost& r, bool spectral) {
   launch_obs_final(e->d_spart, nsblk, e->d_rpart, kRealBlocks, e->d_bins, e->d_counts,
                    spectral ? nbins : 0, e->d_gsum, e->d_out, e->stream);
   LE_TRY(hipGetLastError());
-  const size_t nout = OBS_NTOTAL + (spectral ? 2 * (size_t)nbins : 0);
-  LE_TRY(hipMemcpyAsync(e->h_out, e->d_out, nout * sizeof(double), hipMemcpyDeviceToHost,
-                        e->stream));
   LE_TRY(hipStreamSynchronize(e->stream));
   return LE_OK;
 }
@@ -1056,12 +1133,12 @@ int create_engine(int32_t n, const le_params* ps, const double* const* phi0s,
                        (size_t)e->nsblk_max * e->nbins_max * sizeof(double));
   rc = rc ? rc : alloc((void**)&e->d_gsum, 2 * (size_t)obs_shell_groups(e->nsblk_max) *
                                                e->nbins_max * sizeof(double));
-  rc = rc ? rc : alloc((void**)&e->d_out, nout * sizeof(double));
   if (!rc && hipHostMalloc((void**)&e->h_args, sizeof(StepArgs) * kChunkCap * n) != hipSuccess)
     rc = LE_ENOMEM;
-  if (!rc && hipHostMalloc((void**)&e->h_out, nout * sizeof(double)) != hipSuccess)
+  if (!rc && (hipHostMalloc((void**)&e->h_out, nout * sizeof(double)) != hipSuccess ||
+              hipHostGetDevicePointer((void**)&e->d_out, e->h_out, 0) != hipSuccess))
     rc = LE_ENOMEM;
-  e->stage_bytes = max_real * sizeof(double);
+  e->stage_bytes = max_real * sizeof(double) * (max_real <= Engine::kStageAll ? 3 : 1);
   if (!rc && hipHostMalloc(&e->h_stage, e->stage_bytes) != hipSuccess) rc = LE_ENOMEM;
   // initial state: phi0, omega0 and psi0 from the flow constraint at s = 0
   for (int i = 0; i < n && !rc; ++i) {
@@ -1145,9 +1222,10 @@ int step_engine(Engine* e, int64_t nsteps) {
       }
     }
     LE_TRY(hipGetLastError());
-    LE_TRY(hipStreamSynchronize(e->stream));  // h_args is reused by the next chunk
-    if (e->profiling) harvest_times(e, count);
     remaining -= count;
+    // h_args is reused by the next chunk (after the last, the check below waits)
+    if (remaining > 0 || e->profiling) LE_TRY(hipStreamSynchronize(e->stream));
+    if (e->profiling) harvest_times(e, count);
   }
   if (nsteps > 0) {
     for (const RunHost& r : e->runs) {
@@ -1163,22 +1241,33 @@ int get_state_of(Engine* e, int run, double* phi, double* omega, double* psi, in
   if (!e || run < 0 || run >= e->nruns) return LE_EINVAL;
   const RunHost& r = e->runs[run];
   const Ops& o = e->classes[r.cls].ops;
-  if (phi) LE_RC(download_real(e, r, B_PHI, phi));
-  if (omega) {
-    if (r.inertial) {
-      o.row_c2r(desc(e, r), 1, r.p.ny, B_OM_S, B_OM_R, B_OM_S, B_OM_R, 1,
-                e->classes[r.cls].row_variant, e->stream);
-      LE_TRY(hipGetLastError());
-      LE_RC(download_real(e, r, B_OM_R, omega));
-    } else {
-      std::memset(omega, 0, r.n_real * sizeof(double));
-    }
-  }
-  if (psi) {
-    o.row_c2r(desc(e, r), 1, r.p.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1,
-              e->classes[r.cls].row_variant, e->stream);
-    LE_TRY(hipGetLastError());
-    LE_RC(download_real(e, r, B_PS_R, psi));
+  if (omega && !r.inertial) std::memset(omega, 0, r.n_real * sizeof(double));
+  const bool om = omega && r.inertial;
+  const int rv = e->classes[r.cls].row_variant;
+  if (om && psi)
+    o.row_c2r(desc(e, r), 1, r.p.ny, B_OM_S, B_OM_R, B_PS_S, B_PS_R, 2, rv, e->stream);
+  else if (om)
+    o.row_c2r(desc(e, r), 1, r.p.ny, B_OM_S, B_OM_R, B_OM_S, B_OM_R, 1, rv, e->stream);
+  else if (psi)
+    o.row_c2r(desc(e, r), 1, r.p.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1, rv, e->stream);
+  LE_TRY(hipGetLastError());
+  const int bufs[3] = {B_PHI, B_OM_R, B_PS_R};
+  double* const outs[3] = {phi, om ? omega : nullptr, psi};
+  if (3 * r.n_real * r.tsize <= e->stage_bytes) {
+    // small fields: one wait for all three (64^2, one step and its state: 93 us;
+    // 125 with a wait per field, one after the steps and a copy per snapshot)
+    char* stage = static_cast<char*>(e->h_stage);
+    const size_t bytes = r.n_real * r.tsize;
+    for (int i = 0; i < 3; ++i)
+      if (outs[i])
+        LE_TRY(hipMemcpyAsync(stage + i * bytes, r.buf[bufs[i]], bytes, hipMemcpyDeviceToHost,
+                              e->stream));
+    LE_TRY(hipStreamSynchronize(e->stream));
+    for (int i = 0; i < 3; ++i)
+      if (outs[i]) widen(r, stage + i * bytes, 0, r.n_real, outs[i]);
+  } else {
+    for (int i = 0; i < 3; ++i)
+      if (outs[i]) LE_RC(download_real(e, r, bufs[i], outs[i]));
   }
   if (step) *step = e->step;
   if (wraps) *wraps = r.wraps;
@@ -1276,17 +1365,44 @@ int alloc_snapshots(Engine* e, const RunHost& r) {
   return LE_OK;
 }
 
-// The state between steps: real phi and the row spectra of omega and psi.
+// dst[i] = src[i] for up to three buffers, n 16-byte words in all.
+struct Copy3 {
+  const uint4* src[3];
+  uint4* dst[3];
+  long long end[3];   // words up to and including buffer i
+};
+__global__ __launch_bounds__(256) void k_copy3(Copy3 c) {
+  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < c.end[2]; i += gridDim.x * 256ll) {
+    if (i < c.end[0])
+      c.dst[0][i] = c.src[0][i];
+    else if (i < c.end[1])
+      c.dst[1][i - c.end[0]] = c.src[1][i - c.end[0]];
+    else
+      c.dst[2][i - c.end[1]] = c.src[2][i - c.end[1]];
+  }
+}
+
+// The state between steps: real phi and the row spectra of omega and psi, in
+// one launch.
 int copy_state(Engine* e, const RunHost& r, bool to_snap, int k) {
   const int bufs[3] = {B_PHI, B_OM_S, B_PS_S};
+  // whole 16-byte words: rows are of at least 8 values, fields of 8 rows
   const size_t bytes[3] = {r.n_real * r.tsize, r.n_spec * 2 * r.tsize, r.n_spec * 2 * r.tsize};
+  Copy3 c = {};
+  long long n = 0;
   for (int i = 0; i < 3; ++i) {
     void* live = r.buf[bufs[i]];
     void* snap = e->snap[k][i];
-    if (!live) continue;  // omega's spectrum of a Stokes run
-    LE_TRY(hipMemcpyAsync(to_snap ? snap : live, to_snap ? live : snap, bytes[i],
-                          hipMemcpyDeviceToDevice, e->stream));
+    if (live) {  // no omega spectrum of a Stokes run
+      c.src[i] = static_cast<const uint4*>(to_snap ? live : snap);
+      c.dst[i] = static_cast<uint4*>(to_snap ? snap : live);
+      n += (long long)(bytes[i] / sizeof(uint4));
+    }
+    c.end[i] = n;
   }
+  const long long blocks = std::min<long long>((n + 255) / 256, 2048);
+  hipLaunchKernelGGL(k_copy3, dim3((unsigned)blocks), dim3(256), 0, e->stream, c);
+  LE_TRY(hipGetLastError());
   return LE_OK;
 }
 
