@@ -141,10 +141,11 @@ struct RowLaunch {
       using CB = AdvBatch<T, NX, NR, EF>;
       // FP64 advection: one block per output field (kAdvSplit)
       const dim3 ga(kAdvSplit<T> ? (inertial ? 3 : 2) : 1, gb.y, gb.z);
-      if (mu)
-        hipLaunchKernelGGL((k_mug_batch<T, NX, NR, EF>), gb, dim3(CB::TPB), 0, st, runs, sa,
-                           rows);
-      else if (ny == NX)
+      if (mu) {
+        if constexpr (NR <= 4)
+          hipLaunchKernelGGL((k_mug_batch<T, NX, NR, EF>), gb, dim3(CB::TPB), 0, st, runs, sa,
+                             rows);
+      } else if (ny == NX)
         hipLaunchKernelGGL((k_adv_batch<T, NX, true, NR, EF>), ga, dim3(CB::TPB), 0, st, runs,
                            sa, rows, inertial ? 1 : 0);
       else
@@ -154,7 +155,7 @@ struct RowLaunch {
     }
     return false;
   }
-  // variant kAdvBatch + k (four rows per batch, 16 values per thread),
+  // variant kAdvBatch + k (four or eight rows per batch, 16 values per thread),
   // kAdvBatch2 + k (two, 8), kAdvBatch3 + k (two, 16); k rows per block.
   // False (and *rows set) where the shape does not apply: the caller falls
   // back to the two-kernel strip over k rows.
@@ -168,7 +169,14 @@ struct RowLaunch {
     switch (base) {
       case kAdvBatch3: return batch_shape<2, 16>(mu, runs, sa, ny, gb, *rows, inertial, st);
       case kAdvBatch2: return batch_shape<2, 8>(mu, runs, sa, ny, gb, *rows, inertial, st);
-      default: return batch_shape<4, 16>(mu, runs, sa, ny, gb, *rows, inertial, st);
+      default:
+        // FP32 rows of 4096: eight rows to a batch where the strip holds them (same
+        // LDS per CU as two blocks of four): whole 128-byte runs per store and
+        // 10 rows read for 8 instead of 6 for 4; 4096^2 210 -> 170 us
+        if constexpr (sizeof(T) == 4 && L == 2048)
+          if (!mu && *rows >= 8)
+            return batch_shape<8, 16>(mu, runs, sa, ny, gb, *rows, inertial, st);
+        return batch_shape<4, 16>(mu, runs, sa, ny, gb, *rows, inertial, st);
     }
   }
   // variant 0: the fused bracket kernel (stencil and row transform per

@@ -998,7 +998,7 @@ __global__ __launch_bounds__(NX / 2 / SEG) void k_adv_strip_fft(const Run* __res
   }
 }
 
-// Stage 1a for long rows in batches of NR rows (4 or 2).  The block owns
+// Stage 1a for long rows in batches of NR rows (8, 4 or 2).  The block owns
 // whole rows (NR transform groups of L/EF threads, each thread L/(NR L/EF)
 // x pairs) and walks its strip NR rows at a time.  For each batch and
 // output field (phi_h, f and, with inertia, omega_h) it walks the NR rows,
