@@ -180,16 +180,34 @@ __device__ __forceinline__ void bfly1(c2<T>& a, c2<T>& b) {
 // length-R DFT.  Folded into the DFT's butterflies (decimation in time), level
 // S = 2, 4, .. R needs w^(R/S) exp(-2 pi i k / S), k < S/4 (k = 0 for S = 2),
 // the others being quarter turns of these: R/2 values instead of R - 1
-// powers, formed from w in FP64 (product depth <= 4, error ~1e-15) and rounded
-// once to T.
+// powers, formed in FP64 and rounded once to T.
+//
+// PassIn: what they are formed from, w or, TWO (FP64), w and w^Q of the table.
+// Each squaring doubles a power's relative rounding: from w alone, w^8 carries
+// ten times w's, the larger part of a transform's error (RMS at 2048 points,
+// R = 16: 5.1e-16 from w, 2.8e-16 from w and w^4; R = 8: 3.9e-16 and 2.7e-16;
+// 256 points, R = 4: 2.3e-16 and, w and w^2, 1.9e-16).
+template <typename T, int R, bool TWO_>
+struct PassIn {
+  static constexpr int Q = R >= 8 ? 4 : 2;
+  static constexpr bool TWO = TWO_ && sizeof(T) == 8 && R >= 4;
+  c2<double> w, wq;
+  // entry i (< n / R) of the table exp(-2 pi i k / n), k < n
+  __device__ __forceinline__ void load(gp<const c2<double>> tw, int i) {
+    w = ldg<double>(tw + i);
+    if constexpr (TWO) wq = ldg<double>(tw + Q * i);
+  }
+};
 template <typename T, int R, bool FOLDED = kFolded<T, R>>
 struct PassW {
   static constexpr int N = R >= 4 ? R / 2 : 1;
   c2<T> w[N];  // level R: w[0 .. R/4), level R/2: the next R/8, .., 4: 1, 2: 1
-  __device__ __forceinline__ void set(c2<double> w1) {
-    c2<double> b = w1;  // w^(R/S)
+  template <typename In>
+  __device__ __forceinline__ void set(const In& in) {
+    c2<double> b = in.w;  // w^(R/S)
 #pragma unroll
     for (int S = R; S >= 2; S >>= 1) {
+      if (In::TWO && In::Q * S == R) b = in.wq;
       const int n = S >= 4 ? S / 4 : 1, o = off(S);
 #pragma unroll
       for (int k = 0; k < n; ++k) {
@@ -215,7 +233,9 @@ struct PassW<T, R, false> {
   __device__ __forceinline__ void put(int r, c2<double> a) {
     w[r] = {static_cast<T>(a.x), static_cast<T>(a.y)};
   }
-  __device__ __forceinline__ void set(c2<double> w1) {
+  template <typename In>
+  __device__ __forceinline__ void set(const In& in) {
+    const c2<double> w1 = in.w;
     if constexpr (R >= 2) put(1, w1);
     if constexpr (R >= 4) {
       const c2<double> w2 = cmul(w1, w1), w3 = cmul(w2, w1);
@@ -394,13 +414,14 @@ __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
   if constexpr (L > R0) {
     constexpr int NP = fft_passes(L, E);
     // entry (2L/E)/Ns (t mod Ns): even, below 2L/E, as Ns <= L/E
-    auto tw_of = [&](int Ns) { return ldg<double>(tw + (2 * L / E) / Ns * (t & (Ns - 1))); };
-    c2<double> wn = tw_of(R0);
+    typedef PassIn<T, E, false> In;
+    In wn;
+    wn.load(tw, (2 * L / E) / R0 * (t & (R0 - 1)));
     int Ns = R0;
 #pragma unroll
     for (int pass = 0; pass < NP; ++pass) {
-      const c2<double> w = wn;
-      if (pass + 1 < NP) wn = tw_of(Ns * E);
+      const In w = wn;
+      if (pass + 1 < NP) wn.load(tw, (2 * L / E) / (Ns * E) * (t & (Ns * E - 1)));
       __syncthreads();
 #pragma unroll
       for (int r = 0; r < E; ++r) v[r] = lds[lds_slot<T>(t + r * P) * LS];
@@ -419,33 +440,56 @@ __device__ __forceinline__ void fft_group(c2<T>* v, c2<T>* lds, int LS,
 }
 
 // The passes' twiddles of a kernel that runs several transforms of one length:
-// per pass and thread w = exp(-2 pi i (t mod Ns) / (Ns E)), read from the table
-// once (fft_regs then touches no global memory).  KEEP: what a pass forms from
-// it (PassW) stays in registers (FP32, and up to 8 values in FP64 where LDS and
-// grid leave the registers free); else it is formed at each use, from w in a
-// register or, with LDSW (NT threads), in the thread's own place in LDS.
-template <typename T, int L, int E, int LDSW = 0, bool FOLDED_ = kFolded<T, E>>
+// per pass and thread w = exp(-2 pi i (t mod Ns) / (Ns E)) and, TWO, its power,
+// read from the table once (fft_regs then touches no global memory).  KEEP: what a
+// pass forms from them (PassW) stays in registers (FP32, and up to 8 values in
+// FP64 where LDS and grid leave the registers free); else it is formed at each
+// use, from registers or, with LDSW (NT threads), from the thread's own place in
+// LDS.  SHARED (FP64): one place per t in LDS, filled by the block's first group
+// of P threads for all of them (a read of the table by every group costs a
+// joined kernel 0.2 us per power); load(), a block barrier, then form().
+template <typename T, int L, int E, int LDSW_ = 0, bool FOLDED_ = kFolded<T, E>, bool TWO = true,
+          bool SHARED_ = false>
 struct PassSet {
   static constexpr bool FOLDED = FOLDED_;
+  typedef PassIn<T, E, TWO> In;
   static constexpr int NP = fft_passes(L, E), NPA = NP > 0 ? NP : 1;
   static constexpr bool KEEP = sizeof(T) == 4 || E <= 4 || (E == 8 && L <= 1024);
-  static constexpr int NLDS = !KEEP && LDSW > 0 ? NPA * LDSW : 1;  // values of `area`
-  c2<double> w[KEEP || LDSW > 0 ? 1 : NPA];
+  static constexpr bool SHARED = SHARED_ && sizeof(T) == 8;
+  static constexpr int LDSW = SHARED ? L / E : (KEEP ? 0 : LDSW_);
+  static constexpr int NLDS = LDSW > 0 ? (In::TWO ? 2 : 1) * NPA * LDSW : 1;  // values of `area`
+  In in[KEEP || LDSW > 0 ? 1 : NPA];
   PassW<T, E, FOLDED> pw[KEEP ? NPA : 1];
   c2<double>* area;
   __device__ __forceinline__ void load(gp<const c2<double>> tw, int t, c2<double>* lds = nullptr) {
     int Ns = first_radix(L, E);
-    if constexpr (!KEEP && LDSW > 0) area = lds + threadIdx.x;
+    if constexpr (LDSW > 0) area = lds + (SHARED ? t : (int)threadIdx.x);
+    if (SHARED && (int)threadIdx.x >= LDSW) return;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const c2<double> a = ldg<double>(tw + (2 * L / E) / Ns * (t & (Ns - 1)));
-      if constexpr (KEEP)
+      In a;
+      a.load(tw, (2 * L / E) / Ns * (t & (Ns - 1)));
+      if constexpr (LDSW > 0) {
+        area[p * LDSW] = a.w;
+        if constexpr (In::TWO) area[(NPA + p) * LDSW] = a.wq;
+      } else if constexpr (KEEP) {
         pw[p].set(a);
-      else if constexpr (LDSW > 0)
-        area[p * LDSW] = a;
-      else
-        w[p] = a;
+      } else {
+        in[p] = a;
+      }
       Ns *= E;
+    }
+  }
+  __device__ __forceinline__ In get(int p) const {
+    In a;
+    a.w = area[p * LDSW];
+    if constexpr (In::TWO) a.wq = area[(NPA + p) * LDSW];
+    return a;
+  }
+  __device__ __forceinline__ void form() {
+    if constexpr (SHARED && KEEP) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) pw[p].set(get(p));
     }
   }
   template <int DIR>
@@ -453,9 +497,10 @@ struct PassSet {
     if constexpr (KEEP) {
       dft_tw<T, DIR, E>(v, pw[p]);
     } else {
-      // opaque, so that the compiler does not keep what it forms from it
-      c2<double> a = LDSW > 0 ? area[p * LDSW] : w[LDSW > 0 ? 0 : p];
-      asm volatile("" : "+v"(a.x), "+v"(a.y));
+      In a = LDSW > 0 ? get(p) : in[LDSW > 0 ? 0 : p];
+      // opaque, so that the compiler does not keep what it forms from them
+      asm volatile("" : "+v"(a.w.x), "+v"(a.w.y));
+      if constexpr (In::TWO) asm volatile("" : "+v"(a.wq.x), "+v"(a.wq.y));
       PassW<T, E, FOLDED> f;
       f.set(a);
       dft_tw<T, DIR, E>(v, f);

@@ -28,9 +28,9 @@ namespace le {
 // parts) to the real row, row_c2r's arithmetic without its branch at m = 0
 // (X[0] and X[L] give it by the general formula), left in lds[0 .. L) as pairs
 // and in v.  w0: the table entry t.
-template <typename T, int L, int E, bool WAVE>
-__device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const PassSet<T, L, E>& tw,
-                                         c2<double> w0, int t) {
+template <typename T, int L, int E, bool WAVE, typename TW>
+__device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const TW& tw, c2<double> w0,
+                                         int t) {
   constexpr int P = L / E;
 #pragma unroll
   for (int q = 0; q < E; ++q) {
@@ -56,9 +56,8 @@ __device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const PassSet<T, 
 // Real row pairs v[q] = pair t + q P to the complex transform z of the packed
 // row in lds[0 .. L), and z[0] again in lds[L] (rows_out reads the mirror of
 // m = 0 there).
-template <typename T, int L, int E, bool WAVE>
-__device__ __forceinline__ void rows_r2c_z(c2<T>* v, c2<T>* lds, const PassSet<T, L, E>& tw,
-                                           int t) {
+template <typename T, int L, int E, bool WAVE, typename TW>
+__device__ __forceinline__ void rows_r2c_z(c2<T>* v, c2<T>* lds, const TW& tw, int t) {
   constexpr int P = L / E;
   fft_regs<T, L, E, -1, WAVE>(v, lds, 1, tw, t);
   group_sync<WAVE>();
@@ -83,12 +82,16 @@ struct FuseCfg {
   static constexpr int AR = 2 * (NR + 2) > AG ? 2 * (NR + 2) : AG;  // rows in LDS
   static constexpr int ATPB = AG * P > 64 ? AG * P : 64;
   static constexpr long ALDS = (long)AR * LS * (long)sizeof(c2<T>);
+  // waves per SIMD to compile for: blocks of eight waves that LDS holds twice on a
+  // CU keep to 128 registers (1024-point rows, two to a block)
+  static constexpr int AWPE = E <= 8 && ATPB == 512 && 2 * ALDS + 8192 <= 160L * 1024 ? 4 : 1;
   // mu and g
   static constexpr int MI = NR + 4;
   static constexpr int MG = E >= 8 && MI < 8 ? 8 : MI;  // (E >= 8: at most two pairs per thread)
   static constexpr int MTPB = MG * P > 64 ? MG * P : 64;
   static constexpr long MLDS = (long)MG * LS * (long)sizeof(c2<T>);
-  static constexpr long TAB = (long)TwTab<L>::N * 16;
+  typedef PassSet<T, L, E, 0, kFolded<T, E>, true, (L >= 128)> Tw;
+  static constexpr long TAB = (long)(TwTab<L>::N + Tw::NLDS) * 16;
   static constexpr long LIMIT = 160L * 1024;
   static constexpr bool AOK = ALDS + TAB <= LIMIT && ATPB <= 1024;
   static constexpr bool MOK = MLDS + TAB <= LIMIT && MTPB <= 1024;
@@ -217,13 +220,15 @@ __device__ __forceinline__ void by_diag(int r, int off, F&& f) {
 // Stages 0 and 1 of NR rows per block (file header).  Inverse groups: psi
 // rows j0-1 .. j0+NR, then omega's (inertial); forward groups: field-major.
 template <typename T, int NX, int NR, int NF, int E_>
-__global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB)) void k_flow_adv(
+__global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB),
+                             (FuseCfg<T, NX / 2, NR, NF, E_>::AWPE)) void k_flow_adv(
     const Run* __restrict__ runs, const StepArgs* __restrict__ sa) {
   using C = FuseCfg<T, NX / 2, NR, NF, E_>;
   constexpr int L = C::L, E = C::E, P = C::P, LS = C::LS, NT = C::ATPB;
   constexpr int SEG = (L + NT - 1) / NT;
   __shared__ c2<T> rows[C::AR * LS];
   __shared__ c2<double> wtab[TwTab<L>::N];
+  __shared__ c2<double> wpass[C::Tw::NLDS];
   const BPos bp = block_pos();
   const Run& R = runs[bp.z];
   const Geo& geo = R.g;
@@ -244,8 +249,8 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB)) void k_flow
     for (int r = 0; r < NR + 2; ++r)
       pv[g][r] = ldg<T>(phi + (size_t)wrap_row(j0 - 1 + r, ny) * L + p);
   }
-  PassSet<T, L, E> ptw;
-  ptw.load(tw, t);
+  typename C::Tw ptw;
+  ptw.load(tw, t, wpass);
   const c2<double> w0 = ldg<double>(tw + t);
   tw_tab_fill<L, NT>(wtab, tw);
   const Stencil<T> st = make_stencil<T>(geo, sa[bp.z]);
@@ -269,6 +274,7 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB)) void k_flow
   else
     put_phi(second);
   __syncthreads();
+  ptw.form();
   if (!C::WAVE || grp < C::AI) {  // (a group of several waves holds block barriers)
     c2<T> v[E];
     rows_c2r<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, w0, t);
@@ -374,6 +380,7 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, 2, E_>::MTPB)) void k_phi_m
   constexpr int SEG = (L + NT - 1) / NT;
   __shared__ c2<T> rows[C::MG * LS];
   __shared__ c2<double> wtab[TwTab<L>::N];
+  __shared__ c2<double> wpass[C::Tw::NLDS];
   const BPos bp = block_pos();
   const Run& R = runs[bp.z];
   const Geo& geo = R.g;
@@ -383,8 +390,8 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, 2, E_>::MTPB)) void k_phi_m
   auto tw = to_global<const c2<double>>(R.twx);
   RowsIn<T, L, NR + 4, NT> in;
   in.get(bufp<const c2<T>>(R, B_PHIN), ny, j0 - 2);
-  PassSet<T, L, E> ptw;
-  ptw.load(tw, t);
+  typename C::Tw ptw;
+  ptw.load(tw, t, wpass);
   const c2<double> w0 = ldg<double>(tw + t);
   tw_tab_fill<L, NT>(wtab, tw);
   const MuCoef<T> k = make_mu<T>(geo, sa[bp.z].s);
@@ -393,6 +400,7 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, 2, E_>::MTPB)) void k_phi_m
   const int hp = st.off / 2;
   in.put(rows, LS);
   __syncthreads();
+  ptw.form();
   if (!C::WAVE || grp < C::MI) {
     c2<T> v[E];
     rows_c2r<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, w0, t);

@@ -1558,10 +1558,14 @@ void k_column(const Run* __restrict__ runs, const StepArgs* __restrict__ sa, int
 #pragma unroll
     for (int q = 0; q < E; ++q) u[q] = ldg<T>(in1 + col + (size_t)(t + q * P) * kTW);
   }
-  // 16 values per thread leave no register for the passes' w in FP64 (LDSW); in
-  // FP32 they take the folded form: 4096^2 CH 53.5 us, flow 68.7 (separate
-  // powers formed at each use 57 and 75, kept in registers 56 and, spilling, 104)
-  typedef PassSet<T, L, E, E == 16 ? C::THREADS : 0, kFolded<T, E> || E == 16> Tw;
+  // 16 values per thread leave no register for the passes' w in FP64 (LDSW; the
+  // flow pass takes w alone there: with w^4 4096^2 132 -> 142 us, the CH pass 103
+  // either way); in FP32 they take the folded form: 4096^2 CH 53.5 us, flow 68.7
+  // (separate powers formed at each use 57 and 75, kept in registers 56 and,
+  // spilling, 104)
+  typedef PassSet<T, L, E, E == 16 ? C::THREADS : 0, kFolded<T, E> || E == 16,
+                  !(E == 16 && MODE == COL_FLOW)>
+      Tw;
   __shared__ c2<double> wl[Tw::NLDS];
   Tw ptw;
   ptw.load(tw, t, wl);
