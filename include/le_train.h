@@ -25,7 +25,11 @@ extern "C" {
  *
  * le_cnn_grad: loss = mean over the batch, channels and pixels of (r - t)^2
  *   with r the network's output on x, t the target residual; its gradient
- *   replaces the stored one (and is copied to grad_host when non-NULL).
+ *   replaces the stored one (and is copied to grad_host when non-NULL).  The
+ *   first call with a larger batch than before allocates the workspace for it, on
+ *   the network's device: about 1 KB per pixel of at most 2^20 pixels at
+ *   once (one sample, if larger), less where memory does not allow it; kept until
+ *   le_cnn_destroy.
  * le_cnn_adam: one Adam step with the stored gradient.
  * le_cnn_layer_fwd / le_cnn_layer_bwd (layer 0..3) run one convolution on
  *   pixel-major BF16 inputs a_in_dev [H*W][Cin] (bit patterns): forward gives

@@ -2189,7 +2189,8 @@ int le_cnn_grad(le_cnn* c, const float* xs, const float* ts, int32_t batch, doub
   if (!c || !xs || !ts || batch < 1) return LE_EINVAL;
   hipStream_t st = static_cast<hipStream_t>(stream);
   LE_TRY(hipMemsetAsync(c->net.grad, 0, kCnnParams * sizeof(float), st));
-  if (net_grad(&c->net, xs, ts, batch, loss, st)) return LE_EDEVICE;
+  if (const int rc = net_grad(&c->net, xs, ts, batch, loss, st))
+    return rc == -2 ? LE_ENOMEM : LE_EDEVICE;
   if (grad_host) {
     LE_TRY(hipMemcpyAsync(grad_host, c->net.grad, kCnnParams * sizeof(float),
                           hipMemcpyDeviceToHost, st));

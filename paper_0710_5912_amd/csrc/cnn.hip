@@ -804,9 +804,12 @@ int alloc_dev(void** p, size_t bytes) { return hipMalloc(p, bytes) == hipSuccess
 // The pixel kernels' grid over n pixels (four blocks per CU at most).
 int px_blocks(int n) { return n / 256 < 1024 ? n / 256 : 1024; }
 
+// Tiles of `samples` samples.
+int tiles_of(const Net* n, int samples) { return samples * (n->P / (kFT * kFT)); }
+
 void launch_fwd(const Net* n, int li, int samples, const uint16_t* a_in, float* z,
                 uint16_t* a_out, hipStream_t st) {
-  const int nt = samples * (n->P / (kFT * kFT));
+  const int nt = tiles_of(n, samples);
   const int cap = li ? kFwdBlocks : kConvBlocks;
   const dim3 g(nt < cap ? nt : cap), b(256);
   const float* bias = n->params + kOffB[li];
@@ -821,23 +824,25 @@ void launch_fwd(const Net* n, int li, int samples, const uint16_t* a_in, float* 
                        nt, n->H, n->W, n->lgW);
 }
 
-// The weight gradient's partials: layer l's dw_blocks(l) records at
-// part + dw_part(l).
+// The weight gradient's partials over at most `tiles` tiles: layer l's
+// dw_blocks(l, tiles) records at part + dw_part(l, tiles), layers 1 and 2 in turn
+// in one place (layer 2's are added up before layer 1's are written).
 int dw_blocks(int li, int ntiles) { return ntiles < kDwBlocks[li] ? ntiles : kDwBlocks[li]; }
 int dw_rec(int li) { return kOffB[li] + kCnnCout[li] - kOffW[li]; }
-size_t dw_part(int li) {
-  size_t o = 0;
-  for (int l = 0; l < li; ++l) o += (size_t)kDwBlocks[l] * dw_rec(l);
-  return o;
+size_t dw_part(int li, int tiles) {
+  auto len = [&](int l) { return (size_t)dw_blocks(l, tiles) * dw_rec(l); };
+  return li == 0 ? 0 : li == 3 ? len(0) : len(0) + len(3);
 }
+size_t dw_floats(int tiles) { return dw_part(1, tiles) + (size_t)dw_blocks(1, tiles) * dw_rec(1); }
+static_assert(kDwBlocks[1] == kDwBlocks[2], "layers 1 and 2 share their place");
 
 // Weight and bias gradient partials of layer li over `samples` samples; the
 // input gradient (times silu' of zprev, when given) into dzprev for li > 0.
 void launch_bwd(const Net* n, int li, int samples, const float* dz, const uint16_t* a_in,
                 const float* zprev, float* dzprev, hipStream_t st) {
-  const int nt = samples * (n->P / (kFT * kFT)), nb = dw_blocks(li, nt);
+  const int nt = tiles_of(n, samples), nb = dw_blocks(li, nt);
   const dim3 b(kDwTpb), g(nb);
-  float* part = n->part + dw_part(li);
+  float* part = n->work.part + dw_part(li, tiles_of(n, n->work.samples));
   if (li == 0)
     hipLaunchKernelGGL((k_conv_dw<2, 32>), g, b, 0, st, dz, a_in, part, nt, n->H, n->W, n->lgW);
   else if (li < 3)
@@ -859,8 +864,8 @@ void launch_bwd(const Net* n, int li, int samples, const float* dz, const uint16
 void launch_reduce(const Net* n, int samples, int l0, int l1, hipStream_t st) {
   GradParts p;
   for (int l = 0; l < kCnnLayers; ++l) {
-    p.part[l] = n->part + dw_part(l);
-    p.nb[l] = dw_blocks(l, samples * (n->P / (kFT * kFT)));
+    p.part[l] = n->work.part + dw_part(l, tiles_of(n, n->work.samples));
+    p.nb[l] = dw_blocks(l, tiles_of(n, samples));
   }
   const int e0 = kOffW[l0], e1 = kOffB[l1] + kCnnCout[l1];
   hipLaunchKernelGGL(k_grad_reduce, dim3((e1 - e0 + 63) / 64), dim3(1024), 0, st, p, n->grad, e0,
@@ -874,44 +879,66 @@ void launch_pack_weights(Net* n, hipStream_t st) {
 
 }  // namespace
 
+// The calling thread's current device is `dev` while this lives.
+struct OnDevice {
+  int was = -1;
+  explicit OnDevice(int dev) {
+    if (hipGetDevice(&was) != hipSuccess || was == dev || hipSetDevice(dev) != hipSuccess) was = -1;
+  }
+  ~OnDevice() {
+    if (was >= 0) (void)hipSetDevice(was);
+  }
+};
+
 // Buffers of `samples` samples at once for the training step.
-int train_alloc(TrainWork* w, int P, int samples) {
-  const size_t px = (size_t)P * samples;
+int train_alloc(TrainWork* w, const Net* n, int samples) {
+  const size_t px = (size_t)n->P * samples;
   int rc = 0;
   for (int l = 0; l < kCnnLayers; ++l)
     rc = rc ? rc : alloc_dev((void**)&w->act[l], px * kCnnCin[l] * 2);
   for (int l = 0; l < kCnnLayers; ++l)
     rc = rc ? rc : alloc_dev((void**)&w->z[l], px * kCnnCout[l] * sizeof(float));
   for (int k = 0; k < 2; ++k) rc = rc ? rc : alloc_dev((void**)&w->dz[k], px * 32 * sizeof(float));
+  rc = rc ? rc : alloc_dev((void**)&w->part, dw_floats(tiles_of(n, samples)) * sizeof(float));
   if (!rc) w->samples = samples;
   return rc;
 }
 
 void train_free(TrainWork* w) {
-  void* ps[] = {w->act[0], w->act[1], w->act[2], w->act[3], w->z[0],
-                w->z[1],   w->z[2],   w->z[3],   w->dz[0],  w->dz[1]};
+  void* ps[] = {w->act[0], w->act[1], w->act[2], w->act[3], w->z[0], w->z[1],
+                w->z[2],   w->z[3],   w->dz[0],  w->dz[1],  w->part};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   *w = TrainWork();
 }
 
-// Room for B samples at once, at most kGroupPixels pixels; with less memory
-// than that, for as many as fit (one at least).
+// Room for B samples at once, at most kGroupPixels pixels, on the network's
+// device; with less memory than that, for as many as fit beside what is there,
+// which stays where none do.
 int train_reserve(Net* n, int B) {
+  TrainWork* w = &n->work;
   int want = kGroupPixels / n->P;
   want = want < 1 ? 1 : want > B ? B : want;
-  if (n->work.samples >= want) return 0;
-  train_free(&n->work);
-  for (; want >= 1; want /= 2) {
-    if (!train_alloc(&n->work, n->P, want)) return 0;
-    train_free(&n->work);
+  if (w->asked >= want) return 0;
+  const OnDevice on(n->dev);
+  for (int k = want; k > w->samples; k /= 2) {
+    TrainWork more;
+    if (!train_alloc(&more, n, k)) {
+      train_free(w);
+      *w = more;
+      break;
+    }
+    train_free(&more);
     (void)hipGetLastError();
   }
-  return -2;
+  if (!w->samples) return -2;
+  w->asked = want;
+  return 0;
 }
 
 int net_create(Net* n, int H, int W, bool training) {
   if (H < 16 || W < 16 || (H & (H - 1)) || (W & (W - 1))) return -1;
+  if (hipGetDevice(&n->dev) != hipSuccess) return -3;
   n->H = H;
   n->W = W;
   n->lgW = 0;
@@ -925,6 +952,7 @@ int net_create(Net* n, int H, int W, bool training) {
   for (int l = 0; l < kCnnLayers; ++l) {
     rc = rc ? rc : alloc_dev((void**)&n->wt[l], 32 * (size_t)pad16(9 * kCnnCin[l]) * 2);
     if (l > 0) rc = rc ? rc : alloc_dev((void**)&n->wx[l], 32 * (size_t)pad16(9 * kCnnCout[l]) * 2);
+    if (training) continue;
     rc = rc ? rc : alloc_dev((void**)&n->act[l], P * kCnnCin[l] * 2);
     rc = rc ? rc : alloc_dev((void**)&n->z[l], P * kCnnCout[l] * sizeof(float));
   }
@@ -935,7 +963,6 @@ int net_create(Net* n, int H, int W, bool training) {
     rc = rc ? rc : alloc_dev((void**)&n->grad, kCnnParams * sizeof(float));
     rc = rc ? rc : alloc_dev((void**)&n->m, kCnnParams * sizeof(float));
     rc = rc ? rc : alloc_dev((void**)&n->v, kCnnParams * sizeof(float));
-    rc = rc ? rc : alloc_dev((void**)&n->part, dw_part(kCnnLayers) * sizeof(float));
     rc = rc ? rc : train_reserve(n, 1);
     if (!rc && (hipMemset(n->grad, 0, kCnnParams * 4) || hipMemset(n->m, 0, kCnnParams * 4) ||
                 hipMemset(n->v, 0, kCnnParams * 4)))
@@ -946,7 +973,7 @@ int net_create(Net* n, int H, int W, bool training) {
 }
 
 void net_destroy(Net* n) {
-  void* ps[] = {n->params, n->grad, n->m, n->v, n->part, n->red};
+  void* ps[] = {n->params, n->grad, n->m, n->v, n->red};
   for (void* p : ps)
     if (p) (void)hipFree(p);
   train_free(&n->work);
@@ -969,18 +996,22 @@ int net_set_params(Net* n, const float* host, hipStream_t st) {
 
 int net_forward_planes(Net* n, const float* x, float* r, hipStream_t st) {
   const int P = n->P;
+  const bool training = n->grad != nullptr;
+  uint16_t* const* act = training ? n->work.act : n->act;
+  float* const* z = training ? n->work.z : n->z;
   hipLaunchKernelGGL(k_pack_input, dim3(px_blocks(P)), dim3(256), 0, st, x, P, n->lgP,
-                     n->scales[0], n->scales[1], n->act[0]);
+                     n->scales[0], n->scales[1], act[0]);
   for (int l = 0; l < kCnnLayers; ++l)
-    launch_fwd(n, l, 1, n->act[l], n->z[l], l < 3 ? n->act[l + 1] : nullptr, st);
-  hipLaunchKernelGGL(k_unpack_out, dim3(256), dim3(256), 0, st, n->z[3], P, n->scales[2],
+    launch_fwd(n, l, 1, act[l], z[l], l < 3 ? act[l + 1] : nullptr, st);
+  hipLaunchKernelGGL(k_unpack_out, dim3(256), dim3(256), 0, st, z[3], P, n->scales[2],
                      n->scales[3], r);
   CNN_TRY(hipGetLastError());
   return 0;
 }
 
 int net_grad(Net* n, const float* xs, const float* ts, int B, double* loss, hipStream_t st) {
-  if (!n->grad || B < 1 || train_reserve(n, B)) return -1;
+  if (!n->grad || B < 1) return -1;
+  if (const int rc = train_reserve(n, B)) return rc;
   const int P = n->P;
   const float scale = 2.0f / ((float)B * 2.0f * (float)P);
   const TrainWork& w = n->work;
@@ -997,9 +1028,10 @@ int net_grad(Net* n, const float* xs, const float* ts, int B, double* loss, hipS
     for (int l = kCnnLayers - 1; l >= 0; --l) {
       launch_bwd(n, l, ns, w.dz[cur], w.act[l], l > 0 ? w.z[l - 1] : nullptr,
                  l > 0 ? w.dz[cur ^ 1] : nullptr, st);
+      if (l == 2) launch_reduce(n, ns, 2, 3, st);
       cur ^= 1;
     }
-    launch_reduce(n, ns, 0, kCnnLayers - 1, st);
+    launch_reduce(n, ns, 0, 1, st);
   }
   CNN_TRY(hipGetLastError());
   double h = 0.0;

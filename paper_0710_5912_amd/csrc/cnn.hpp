@@ -23,18 +23,21 @@ constexpr int kCnnCin[kCnnLayers] = {2, 32, 32, 32};
 constexpr int kCnnCout[kCnnLayers] = {32, 32, 32, 2};
 constexpr int kCnnParams = 2 * 32 * 9 + 32 + 32 * 32 * 9 + 32 + 32 * 32 * 9 + 32 + 32 * 2 * 9 + 2;
 
-// What a training step keeps of `samples` samples at once (grown to the batch
-// on first use, at most 2^20 pixels).
+// What a training step keeps of `samples` samples at once (one from the start,
+// grown to the batch on its first use, at most 2^20 pixels; `asked`: the largest
+// number wanted so far, more than `samples` where memory did not allow it).
 struct TrainWork {
-  int samples = 0;
+  int samples = 0, asked = 0;
   uint16_t* act[kCnnLayers] = {};  // inputs of each layer, BF16 [px][Cin]
   float* z[kCnnLayers] = {};       // pre-activations FP32 [px][Cout]
   float* dz[2] = {};               // gradient ping-pong FP32 [px][32]
+  float* part = nullptr;           // weight-gradient partials
 };
 
-// Network state on one device (weights, one sample's buffers for a grid of
-// H x W pixels and, when training, optimiser state and the step's workspace).
+// Network state on one device (weights and, for a grid of H x W pixels, one
+// sample's buffers or, when training, optimiser state and the workspace).
 struct Net {
+  int dev = 0;                  // the device current at creation
   int H = 0, W = 0, P = 0, lgW = 0, lgP = 0;   // P = H W pixels
   float* params = nullptr;      // FP32 master, kCnnParams
   float* grad = nullptr;        // FP32, kCnnParams
@@ -43,10 +46,9 @@ struct Net {
   uint16_t* wt[kCnnLayers] = {};   // forward operands  [32][KP]
   uint16_t* wx[kCnnLayers] = {};   // input-grad operands [32][KPX] (layers 1..3)
   float scales[4] = {1.f, 1.f, 1.f, 1.f};   // in_phi, in_omega, out_phi, out_omega
-  uint16_t* act[kCnnLayers] = {};  // inputs of each layer, BF16 [P][Cin]
-  float* z[kCnnLayers] = {};       // pre-activations FP32 [P][Cout]
-  float* part = nullptr;           // weight-gradient partials
-  TrainWork work;
+  uint16_t* act[kCnnLayers] = {};  // inputs of each layer, BF16 [P][Cin] (not training)
+  float* z[kCnnLayers] = {};       // pre-activations FP32 [P][Cout] (not training)
+  TrainWork work;                  // (training)
   double* red = nullptr;           // reduction scratch (FP64)
   int64_t adam_t = 0;
 };

@@ -1,0 +1,94 @@
+"""Host code of the library against a stub of the HIP runtime (hip_stub.c): two
+devices in host memory, kernels that do nothing.  What is allocated, where and
+when; which device's handles a call uses.  Each test runs in a child process
+that loads the stub before the library.
+"""
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_0710_5912_amd", "libmodelh.so")
+
+HEAD = """
+import ctypes as C, sys
+stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+stub.stub_used.restype = C.c_size_t
+stub.stub_mallocs.restype = stub.stub_events.restype = C.c_long
+stub.stub_limit.argtypes = [C.c_size_t]
+lib = C.CDLL(sys.argv[2])
+used = lambda: [stub.stub_used(d) for d in range(2)]
+def net(h, w):
+    p = C.c_void_p()
+    assert lib.le_cnn_create(h, w, C.byref(p)) == 0
+    return p
+def grad(p, batch, h, w):
+    x = (C.c_float * (2 * h * w * batch))()
+    loss = C.c_double()
+    return lib.le_cnn_grad(p, x, x, batch, C.byref(loss), None, None)
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    cc = shutil.which("gcc")
+    if cc is None or not os.path.exists(LIB):
+        pytest.skip("no host compiler, or the library is not built")
+    out = str(tmp_path_factory.mktemp("stub") / "hip_stub.so")
+    subprocess.run([cc, "-O1", "-shared", "-fPIC", "-pthread", "-o", out,
+                    os.path.join(ROOT, "tests", "hip_stub.c")], check=True)
+    return out
+
+
+def child(stub, body):
+    r = subprocess.run([sys.executable, "-c", HEAD + body, stub, LIB], capture_output=True,
+                       text=True, timeout=120, cwd=ROOT)
+    assert r.returncode == 0, r.stderr
+
+
+def test_training_workspace_is_on_the_networks_device(stub):
+    child(stub, """
+stub.hipSetDevice(1)
+n = net(32, 32)
+before = used()
+stub.hipSetDevice(0)
+assert grad(n, 8, 32, 32) == 0
+dev = C.c_int()
+stub.hipGetDevice(C.byref(dev))
+assert dev.value == 0
+assert used()[0] == 0 and used()[1] > before[1], used()
+lib.le_cnn_destroy(n)
+assert used() == [0, 0], used()
+""")
+
+
+@pytest.mark.parametrize("h,w", [(16, 16), (64, 32), (256, 256), (1024, 1024)])
+def test_training_network_holds_one_samples_buffers(stub, h, w):
+    """844 bytes per pixel (activations, pre-activations, two gradients) and 144 for
+    the weight gradient's partials, what one layer's take; 2 MB for the rest."""
+    child(stub, f"""
+n = net({h}, {w})
+assert used()[0] <= (844 + 144) * {h * w} + (2 << 20), used()
+""")
+
+
+def test_training_workspace_settles_where_memory_is_short(stub):
+    """16 samples of 64^2 do not fit, 8 do: they are taken once and kept."""
+    child(stub, """
+n = net(64, 64)
+stub.stub_limit(used()[0] + 12 * 900 * 64 * 64)
+assert grad(n, 16, 64, 64) == 0
+held, calls = used(), stub.stub_mallocs()
+assert held[0] > 8 * 844 * 64 * 64
+assert grad(n, 16, 64, 64) == 0 and grad(n, 16, 64, 64) == 0
+assert used() == held and stub.stub_mallocs() == calls
+stub.stub_limit(1 << 62)
+assert grad(n, 32, 64, 64) == 0 and used()[0] > 32 * 844 * 64 * 64
+lib.le_cnn_destroy(n)
+assert used() == [0, 0]
+""")
