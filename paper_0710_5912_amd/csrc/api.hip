@@ -215,7 +215,8 @@ struct le_ctx {
                                  // it up to kStageAll values)
   static constexpr size_t kStageAll = (size_t)1 << 18;
   static constexpr int kSegs = 4;
-  hipEvent_t seg_ev[kSegs] = {};  // download_real's segments
+  hipEvent_t seg_ev[kSegs] = {};  // download_real's segments (made at creation:
+                                  // events belong to the device current then)
   size_t stage_bytes = 0;
   bool use_graphs = true;
   std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
@@ -393,8 +394,6 @@ int download_real(Engine* e, const RunHost& r, int b, double* dst) {
     return LE_OK;
   }
   constexpr int kSegs = Engine::kSegs;
-  for (hipEvent_t& ev : e->seg_ev)
-    if (!ev) LE_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   auto cut = [&](int s) { return r.n_real * s / kSegs; };
   hipError_t err = hipSuccess;
   for (int s = 0; s < kSegs && err == hipSuccess; ++s) {
@@ -1140,6 +1139,10 @@ int create_engine(int32_t n, const le_params* ps, const double* const* phi0s,
     rc = LE_ENOMEM;
   e->stage_bytes = max_real * sizeof(double) * (max_real <= Engine::kStageAll ? 3 : 1);
   if (!rc && hipHostMalloc(&e->h_stage, e->stage_bytes) != hipSuccess) rc = LE_ENOMEM;
+  for (hipEvent_t& ev : e->seg_ev)
+    if (!rc && max_real >= 2 * kCopySlice &&
+        hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess)
+      rc = LE_EDEVICE;
   // initial state: phi0, omega0 and psi0 from the flow constraint at s = 0
   for (int i = 0; i < n && !rc; ++i) {
     RunHost& r = e->runs[i];

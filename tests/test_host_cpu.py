@@ -92,3 +92,25 @@ assert grad(n, 32, 64, 64) == 0 and used()[0] > 32 * 844 * 64 * 64
 lib.le_cnn_destroy(n)
 assert used() == [0, 0]
 """)
+
+
+def test_large_fields_are_read_back_from_any_threads_device(stub):
+    """A context of device 1 read by a thread whose current device is 0: what the
+    call waits on belongs to the context's device."""
+    child(stub, """
+import threading
+sys.path.insert(0, ".")
+from paper_0710_5912_amd import le
+p = le.make_params(dict(nx=1024, ny=512, lx=1024.0, ly=512.0, gdot=0.01, A=1.0, B=1.0, kappa=1.0,
+                        M=1.0, eta=1.0, rho=1.0, dt=0.005))
+phi = (C.c_double * (1024 * 512))()
+c, rc = C.c_void_p(), []
+stub.hipSetDevice(1)
+assert lib.le_create(C.byref(p), phi, None, C.byref(c)) == 0
+read = lambda: rc.append(lib.le_get_state(c, phi, phi, phi, None, None))   # a new thread: device 0
+t = threading.Thread(target=read)
+t.start()
+t.join()
+assert rc == [0], rc
+lib.le_destroy(c)
+""")
