@@ -27,33 +27,38 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E, vendor figure
 METRIC = "site-updates/s/GPU (plain FP64 vs FP32, batched, learned corrector) at stated L(t) error"
 
 
-def stage_bytes(params, precision):
-    """Algorithmic HBM bytes per launch of each stage (compulsory reads + writes)."""
+def stage_bytes(params, precision, joined=()):
+    """Algorithmic HBM bytes per launch of each stage (compulsory reads + writes);
+    a pair of joined stages is one entry, "a+b", without what it keeps on chip."""
     w = 8 if precision == "fp64" else 4
     nx, ny = params["nx"], params["ny"]
     real = nx * ny * w
     spec = ny * (nx // 2 + 1) * 2 * w
-    if params["rho"] > 0:
-        return {
-            "row_inv_flow": 2 * spec + 2 * real,
-            "advect": 3 * real + 3 * spec,
-            "column_ch": 3 * spec,
-            "row_inv_phi": spec + real,
-            "mu_source": real + spec,
-            "column_flow": 4 * spec,
-        }
-    return {
-        "row_inv_flow": spec + real,
-        "advect": 2 * real + 2 * spec,
+    flow = 2 if params["rho"] > 0 else 1        # omega and psi, or psi
+    b = {
+        "row_inv_flow": flow * (spec + real),
+        "advect": (flow + 1) * (real + spec),
         "column_ch": 3 * spec,
         "row_inv_phi": spec + real,
         "mu_source": real + spec,
-        "column_flow": 2 * spec,
+        "column_flow": 2 * flow * spec,
     }
+    kept = {("row_inv_flow", "advect"): 2 * flow * real,   # neither written nor read back
+            ("row_inv_phi", "mu_source"): real}            # written (the state), not read back
+    return join(b, joined, lambda pair, v: v - kept[pair])
 
 
-def step_bytes(params, precision):
-    return sum(stage_bytes(params, precision).values())
+def join(d, joined, f=lambda pair, v: v):
+    """d with the entries of each joined pair of stages added up, then f of the sum."""
+    second = {b: (a, b) for a, b in joined}
+    first = {a for a, _ in joined}
+    return {("+".join(second[k]) if k in second else k):
+            (f(second[k], d[second[k][0]] + v) if k in second else v)
+            for k, v in d.items() if k not in first}
+
+
+def step_bytes(params, precision, joined=()):
+    return sum(stage_bytes(params, precision, joined).values())
 
 
 def four_pass_bytes(params, precision):
@@ -96,8 +101,9 @@ def run_variant(le, torch, params, precision, steps, warmup, obs_every, seed=0,
     each call), bracketed by HIP events on the library's stream.  Warm-up: W
     steps, then one call of every distinct length of the plan and one
     observables call, so no graph is captured inside the clock.  Then each
-    stage timed on its own: stage_reps back-to-back launches of its autotuned
-    kernels between HIP events on the same stream."""
+    kernel of the step (one per stage, or per pair of joined stages) timed on
+    its own: stage_reps back-to-back launches between HIP events on the same
+    stream."""
     from paper_0710_5912_amd import inputs
 
     nx, ny = params["nx"], params["ny"]
@@ -125,12 +131,12 @@ def run_variant(le, torch, params, precision, steps, warmup, obs_every, seed=0,
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     gpu_ms = e0.elapsed_time(e1)
-    times = {}
+    times, joined = {}, ctx.joined()
     if stage_reps:
-        times = {s: ctx.time_stage(s, stage_reps) for s in le.STAGES}
+        times = join({s: ctx.time_stage(s, stage_reps) for s in le.STAGES}, joined)
     tuning = ctx.tuning()[0]
-    out = dict(wall=wall, gpu_ms=gpu_ms, times=times, series=series, tuning=tuning,
-               steps_before=step0, obs_calls=len(plan), last_obs=o, last_sk=sk)
+    out = dict(wall=wall, gpu_ms=gpu_ms, times=times, joined=joined, series=series,
+               tuning=tuning, steps_before=step0, obs_calls=len(plan), last_obs=o, last_sk=sk)
     if keep:
         out["ctx"] = ctx
     else:
@@ -154,7 +160,7 @@ def batch_shape(v):
 
 
 def stage_kernels(tuning, inertial):
-    """Kernels each stage launches under the autotuned variants."""
+    """Kernels each stage (or joined pair) launches under the autotuned variants."""
     a, nx = tuning["advect"], tuning["nx"]
     if a == 0:
         adv = "k_bracket"
@@ -178,12 +184,13 @@ def stage_kernels(tuning, inertial):
         mu = "k_mug_strip + k_row_r2c"
     return {"row_inv_flow": "k_row_c2r", "advect": adv, "column_ch": "k_column<COL_CH>",
             "row_inv_phi": "k_row_c2r", "mu_source": mu,
-            "column_flow": "k_column<COL_FLOW>" if inertial else "k_column<COL_STOKES>"}
+            "column_flow": "k_column<COL_FLOW>" if inertial else "k_column<COL_STOKES>",
+            "row_inv_flow+advect": "k_flow_adv", "row_inv_phi+mu_source": "k_phi_mu"}
 
 
-def roofline_rows(params, precision, times):
-    """Per stage: average launch us, algorithmic bytes and GB/s; the dominant stage."""
-    b = stage_bytes(params, precision)
+def roofline_rows(params, precision, times, joined):
+    """Per stage or joined pair: average launch us, algorithmic bytes and GB/s; the dominant one."""
+    b = stage_bytes(params, precision, joined)
     rows = {k: dict(avg_us=us, bytes=b[k], gbs=b[k] / (us * 1e-6) / 1e9)
             for k, us in times.items()}
     if not rows:
@@ -419,11 +426,12 @@ def cpu_baseline(params):
 
 
 def variant_entry(params, precision, rv, steps, sites):
-    d, rw = roofline_rows(params, precision, rv["times"])
+    d, rw = roofline_rows(params, precision, rv["times"], rv["joined"])
     ms = rv["gpu_ms"] / steps
     return dict(value=sites * steps / (rv["gpu_ms"] * 1e-3), ms_per_step=ms,
                 dominant=d, dominant_frac=rw[d]["gbs"] / HBM_PEAK_GBS,
-                step_frac=step_bytes(params, precision) / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                step_frac=step_bytes(params, precision, rv["joined"]) / (ms * 1e-3) / 1e9
+                / HBM_PEAK_GBS,
                 step_frac_four_pass=four_pass_bytes(params, precision) / (ms * 1e-3) / 1e9
                 / HBM_PEAK_GBS,
                 tuning=rv["tuning"], obs_calls=rv["obs_calls"],
@@ -483,7 +491,7 @@ def main():
     pcie = host_transfer(r.pop("ctx"), sites, args.steps, r["gpu_ms"])
     copy_gbs = copy_bandwidth(torch)
     value = sites * args.steps / (r["gpu_ms"] * 1e-3)
-    dom, rows = roofline_rows(params, prec, r["times"])
+    dom, rows = roofline_rows(params, prec, r["times"], r["joined"])
     ms_step = r["gpu_ms"] / args.steps
     o = r["last_obs"]
     out = {
@@ -525,10 +533,10 @@ def main():
                      "frac_of_copy": rows[dom]["gbs"] / copy_gbs},
         "stages": {k: {"avg_us": round(v["avg_us"], 2), "GBs": round(v["gbs"], 1)}
                    for k, v in rows.items()},
-        "step_roofline": {"bytes_per_step": step_bytes(params, prec),
+        "step_roofline": {"bytes_per_step": step_bytes(params, prec, r["joined"]),
                           "bytes_per_step_four_pass_minimum": four_pass_bytes(params, prec),
-                          "frac": step_bytes(params, prec) / (ms_step * 1e-3) / 1e9
-                          / HBM_PEAK_GBS,
+                          "frac": step_bytes(params, prec, r["joined"]) / (ms_step * 1e-3)
+                          / 1e9 / HBM_PEAK_GBS,
                           "frac_four_pass_minimum": four_pass_bytes(params, prec)
                           / (ms_step * 1e-3) / 1e9 / HBM_PEAK_GBS},
         "last_observables": {k: o[k] for k in ("step", "t", "mean_phi", "Ls", "L_par",

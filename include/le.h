@@ -242,9 +242,10 @@ const char* le_last_error(void);
  *   0 inverse row transform of omega and psi    3 inverse row transform of phi
  *   1 advection + forward row transforms (1a)    4 mu and g + forward row transform (2a)
  *   2 column pass, Cahn-Hilliard update (1b)     5 column pass, omega and psi (2b, 3)
- * Unprofiled steps of most grids join stage 0 to 1 and stage 3 to 4 in one
- * kernel each; with profiling enabled they stay apart, so that each has a time
- * of its own (the same step, to rounding).
+ * On most grids one kernel does stages 0 and 1, and one stages 3 and 4
+ * (le_joined).  The time of such a kernel is divided evenly between its two
+ * stages: only their sum is measured.  Timed steps run the kernels that untimed
+ * ones run, with the same results.
  * le_profile(c, 1) enables and clears the counters, le_profile(c, 0) disables.
  * le_stage_times writes min(cap, LE_NSTAGES) accumulated milliseconds and
  * launch counts (either pointer may be NULL).
@@ -258,11 +259,20 @@ int le_stage_times(le_ctx* c, double* ms, int64_t* launches, int32_t cap);
  * `stage` (numbered as above, with the autotuned variant) over `reps`
  * back-to-back launches on the context's stream, after one untimed launch.
  * The launches read the current state and write only scratch buffers, so
- * the state is neither advanced nor changed.
+ * the state is neither advanced nor changed.  For either stage of a joined
+ * kernel: half of its duration.
  * LE_EINVAL for a bad stage, reps < 1 or NULL; LE_ESTATE while le_profile
  * timing is enabled.
  */
 int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch);
+
+/*
+ * le_joined: which stages of the context's step share a kernel: bit 0 stages 0
+ * and 1, bit 1 stages 3 and 4 (LE_EINVAL for NULL).  Fixed by the grid, the
+ * precision, the scheme (the upwind advection is a kernel of its own) and the
+ * LE_TUNE_* variables at creation (below).
+ */
+int le_joined(le_ctx* c);
 
 /*
  * Kernel variants (not part of the method: how its stages are laid out on
@@ -294,9 +304,11 @@ int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch)
  * same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
  * that text file across processes, LE_TUNE_CACHE=off times every creation
  * afresh.  Choices fixed through LE_TUNE_* are not cached.
- * advect, mu_source, row and row_fwd are those of the separate row stages, which
- * a step runs under le_profile, for the upwind scheme, on rows too long for the
- * joined kernels, and where LE_TUNE_ADV, _MU, _ROW or _ROW_FWD fixes one.
+ * advect and mu_source are those of the stages' own kernels, which a step runs
+ * where le_joined does not join the stage to the one before: on rows too long for
+ * the joined kernels, for the upwind advection, and where LE_TUNE_ADV, _MU, _ROW
+ * or _ROW_FWD fixes a variant.  row also serves le_get_state and corrected steps,
+ * row_fwd the observables, corrected steps and the upwind advection.
  */
 enum { LE_TUNING_FIELDS = 10 };
 int le_tuning(le_ctx* c, int32_t* out, int32_t cap);

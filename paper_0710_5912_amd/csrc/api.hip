@@ -180,6 +180,9 @@ struct Class {
   bool upwind3 = false;      // LE_SCHEME_UPWIND3: the upwind advection kernel
   bool banded = false;       // LE_SCHEME_BANDED: the banded column kernels
   int advect() const { return upwind3 ? kAdvUpwind : adv_variant; }
+  // stages 0 and 1 (3 and 4) in one kernel
+  bool joined_adv() const { return fuse_adv != FUSE_NONE && !upwind3; }
+  bool joined_mu() const { return fuse_mu != FUSE_NONE; }
   // Ops::column with the banded flag of the scheme
   void column(int mode, const Run* runs, int nruns, int nx, const StepArgs* sa, int bin0,
               int bin1, int bout0, int bout1, int variant, hipStream_t st) const {
@@ -221,7 +224,7 @@ struct le_ctx {
   bool use_graphs = true;
   std::map<int64_t, std::pair<hipGraph_t, hipGraphExec_t>> graphs;
   bool profiling = false;
-  std::vector<hipEvent_t> events;  // kProfChunk * (LE_NSTAGES + 1)
+  std::vector<hipEvent_t> events;  // kProfChunk * kMarks
   double stage_ms[LE_NSTAGES] = {0};
   int64_t stage_n[LE_NSTAGES] = {0};
   Net* net = nullptr;              // learned corrector (single inertial run)
@@ -454,56 +457,86 @@ int solve_psi(Engine* e, const RunHost& r) {
   return LE_OK;
 }
 
-void enqueue_runs_step(const Class& k, const Run* d, int n, const StepArgs* a, hipStream_t st,
-                       bool inverse = true);
+// One stage of a step of n runs of class k (descriptors d, StepArgs a).  Stages
+// that share a kernel are launched under the second one's number.
+void enqueue_stage(const Class& k, int stage, const Run* d, int n, const StepArgs* a,
+                   hipStream_t st) {
+  switch (stage) {
+    case 0:
+      if (k.joined_adv()) break;
+      if (k.inertial)
+        k.ops.row_c2r(d, n, k.ny, B_OM_S, B_OM_R, B_PS_S, B_PS_R, 2, k.row_variant, st);
+      else
+        k.ops.row_c2r(d, n, k.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1, k.row_variant, st);
+      break;
+    case 1:
+      if (k.joined_adv())
+        (void)k.ops.flow_adv(d, n, k.ny, a, k.inertial, k.fuse_adv, st);
+      else
+        k.ops.advect(d, n, k.ny, a, k.inertial, k.advect(), k.row_fwd_variant, st);
+      break;
+    case 2:
+      k.column(COL_CH, d, n, k.nx, a, B_PHIH, B_FH, B_PHIN, B_PHIN, k.col_ch_variant, st);
+      break;
+    case 3:
+      if (!k.joined_mu()) k.ops.row_c2r(d, n, k.ny, B_PHIN, B_PHI, B_PHIN, B_PHI, 1, k.row_variant, st);
+      break;
+    case 4:
+      if (k.joined_mu())
+        (void)k.ops.phi_mu(d, n, k.ny, a, k.fuse_mu, st);
+      else
+        k.ops.mu_source(d, n, k.ny, a, k.mu_variant, k.row_fwd_variant, st);
+      break;
+    default:
+      if (k.inertial)
+        k.column(COL_FLOW, d, n, k.nx, a, B_OMH, B_GH, B_OM_S, B_PS_S, k.col_flow_variant, st);
+      else
+        k.column(COL_STOKES, d, n, k.nx, a, B_GH, B_GH, B_PS_S, B_PS_S, k.col_flow_variant, st);
+      break;
+  }
+}
 
-// The stages of one step for every run; sa: the step's row of the table.
-// ev: LE_NSTAGES + 1 events recorded around the stages when timing.
+// One step of n runs of class k; with inverse == false the real omega and psi
+// are taken as they are (stage 0 is skipped).
+void enqueue_runs_step(const Class& k, const Run* d, int n, const StepArgs* a, hipStream_t st,
+                       bool inverse = true) {
+  if (!inverse) k.ops.advect(d, n, k.ny, a, k.inertial, k.advect(), k.row_fwd_variant, st);
+  for (int s = inverse ? 0 : 2; s < LE_NSTAGES; ++s) enqueue_stage(k, s, d, n, a, st);
+}
+
+// A step with its stages timed: kMarks events, between them what kTimed lists,
+// one stage of the classes that run it apart or joined (`joined`: its kernel
+// holds the stage before it too).
+struct Timed {
+  int stage;
+  bool joined;
+};
+constexpr Timed kTimed[] = {{0, false}, {1, false}, {1, true}, {2, false},
+                            {3, false}, {4, false}, {4, true}, {5, false}};
+constexpr int kMarks = sizeof(kTimed) / sizeof(kTimed[0]) + 1;
+// Whether class k launches anything in that interval.
+bool runs_in(const Class& k, Timed i) {
+  const bool joined = i.stage <= 1 ? k.joined_adv()
+                                   : (i.stage == 3 || i.stage == 4) && k.joined_mu();
+  return joined == i.joined;
+}
+
+// One step for every run; sa: the step's row of the table.  ev: kMarks events
+// recorded around the stages when timing.
 void enqueue_step(Engine* e, const StepArgs* sa, hipEvent_t* ev) {
-  auto mark = [&](int k) {
-    if (ev) (void)hipEventRecord(ev[k], e->stream);
-  };
   hipStream_t st = e->stream;
   if (!ev) {
     for (const Class& k : e->classes)
       enqueue_runs_step(k, e->d_desc + k.first, (int)k.members.size(), sa + k.first, st);
     return;
   }
-  mark(0);
-  for (const Class& k : e->classes) {
-    const Run* d = e->d_desc + k.first;
-    const int n = (int)k.members.size();
-    if (k.inertial)
-      k.ops.row_c2r(d, n, k.ny, B_OM_S, B_OM_R, B_PS_S, B_PS_R, 2, k.row_variant, st);
-    else
-      k.ops.row_c2r(d, n, k.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1, k.row_variant, st);
+  (void)hipEventRecord(*ev++, st);
+  for (const Timed i : kTimed) {
+    for (const Class& k : e->classes)
+      if (runs_in(k, i))
+        enqueue_stage(k, i.stage, e->d_desc + k.first, (int)k.members.size(), sa + k.first, st);
+    (void)hipEventRecord(*ev++, st);
   }
-  mark(1);
-  for (const Class& k : e->classes)
-    k.ops.advect(e->d_desc + k.first, (int)k.members.size(), k.ny, sa + k.first, k.inertial,
-                 k.advect(), k.row_fwd_variant, st);
-  mark(2);
-  for (const Class& k : e->classes)
-    k.column(COL_CH, e->d_desc + k.first, (int)k.members.size(), k.nx, sa + k.first,
-                 B_PHIH, B_FH, B_PHIN, B_PHIN, k.col_ch_variant, st);
-  mark(3);
-  for (const Class& k : e->classes)
-    k.ops.row_c2r(e->d_desc + k.first, (int)k.members.size(), k.ny, B_PHIN, B_PHI, B_PHIN,
-                  B_PHI, 1, k.row_variant, st);
-  mark(4);
-  for (const Class& k : e->classes)
-    k.ops.mu_source(e->d_desc + k.first, (int)k.members.size(), k.ny, sa + k.first,
-                    k.mu_variant, k.row_fwd_variant, st);
-  mark(5);
-  for (const Class& k : e->classes) {
-    if (k.inertial)
-      k.column(COL_FLOW, e->d_desc + k.first, (int)k.members.size(), k.nx, sa + k.first,
-                   B_OMH, B_GH, B_OM_S, B_PS_S, k.col_flow_variant, st);
-    else
-      k.column(COL_STOKES, e->d_desc + k.first, (int)k.members.size(), k.nx,
-                   sa + k.first, B_GH, B_GH, B_PS_S, B_PS_S, k.col_flow_variant, st);
-  }
-  mark(6);
 }
 
 // Enqueue `count` steps whose StepArgs rows are d_args[0 .. count).  Chunks
@@ -586,40 +619,11 @@ int enqueue_chunk(Engine* e, int64_t key, int64_t count, F&& enqueue_one) {
     return LE_OK;
   }
   for (int64_t k = 0; k < count; ++k)
-    LE_RC(enqueue_one(k, e->profiling ? &e->events[(size_t)k * (LE_NSTAGES + 1)] : nullptr));
+    LE_RC(enqueue_one(k, e->profiling ? &e->events[(size_t)k * kMarks] : nullptr));
   return LE_OK;
 }
 
-// One step of one class on stream st (the stages of enqueue_step).
-// The stages of one step of n runs of class k (descriptors d, StepArgs a);
-// with inverse == false the real omega and psi are taken as they are (the
-// inverse row transforms of stage 0 are skipped).
-void enqueue_runs_step(const Class& k, const Run* d, int n, const StepArgs* a, hipStream_t st,
-                       bool inverse) {
-  const bool fused = inverse && k.fuse_adv != FUSE_NONE && !k.upwind3;
-  if (fused) {
-    (void)k.ops.flow_adv(d, n, k.ny, a, k.inertial, k.fuse_adv, st);
-  } else if (inverse) {
-    if (k.inertial)
-      k.ops.row_c2r(d, n, k.ny, B_OM_S, B_OM_R, B_PS_S, B_PS_R, 2, k.row_variant, st);
-    else
-      k.ops.row_c2r(d, n, k.ny, B_PS_S, B_PS_R, B_PS_S, B_PS_R, 1, k.row_variant, st);
-  }
-  if (!fused) k.ops.advect(d, n, k.ny, a, k.inertial, k.advect(), k.row_fwd_variant, st);
-  k.column(COL_CH, d, n, k.nx, a, B_PHIH, B_FH, B_PHIN, B_PHIN, k.col_ch_variant, st);
-  if (k.fuse_mu != FUSE_NONE) {
-    (void)k.ops.phi_mu(d, n, k.ny, a, k.fuse_mu, st);
-  } else {
-    k.ops.row_c2r(d, n, k.ny, B_PHIN, B_PHI, B_PHIN, B_PHI, 1, k.row_variant, st);
-    k.ops.mu_source(d, n, k.ny, a, k.mu_variant, k.row_fwd_variant, st);
-  }
-  if (k.inertial)
-    k.column(COL_FLOW, d, n, k.nx, a, B_OMH, B_GH, B_OM_S, B_PS_S, k.col_flow_variant, st);
-  else
-    k.column(COL_STOKES, d, n, k.nx, a, B_GH, B_GH, B_PS_S, B_PS_S, k.col_flow_variant,
-                 st);
-}
-
+// One step of one class on stream st.
 void enqueue_class_step(const Engine* e, const Class& k, const StepArgs* sa, hipStream_t st) {
   enqueue_runs_step(k, e->d_desc + k.first, (int)k.members.size(), sa + k.first, st);
 }
@@ -671,14 +675,18 @@ void enqueue_remap(Engine* e, const RunHost& r, int64_t dk) {
 
 void harvest_times(Engine* e, int64_t count) {
   for (int64_t k = 0; k < count; ++k) {
-    hipEvent_t* ev = &e->events[(size_t)k * (LE_NSTAGES + 1)];
-    for (int s = 0; s < LE_NSTAGES; ++s) {
+    hipEvent_t* ev = &e->events[(size_t)k * kMarks];
+    for (const Timed i : kTimed) {
+      bool any = false;
+      for (const Class& c : e->classes) any = any || runs_in(c, i);
       float ms = 0.f;
-      if (hipEventElapsedTime(&ms, ev[s], ev[s + 1]) == hipSuccess) {
-        e->stage_ms[s] += ms;
-        e->stage_n[s] += 1;
+      if (any && hipEventElapsedTime(&ms, ev[0], ev[1]) == hipSuccess) {
+        e->stage_ms[i.stage] += i.joined ? 0.5 * ms : ms;
+        if (i.joined) e->stage_ms[i.stage - 1] += 0.5 * ms;
       }
+      ++ev;
     }
+    for (int64_t& n : e->stage_n) ++n;
   }
 }
 
@@ -1280,7 +1288,7 @@ int get_state_of(Engine* e, int run, double* phi, double* omega, double* psi, in
 int profile_engine(Engine* e, int enable) {
   if (!e) return LE_EINVAL;
   if (enable && e->events.empty()) {
-    e->events.assign((size_t)kProfChunk * (LE_NSTAGES + 1), nullptr);
+    e->events.assign((size_t)kProfChunk * kMarks, nullptr);
     for (auto& ev : e->events) LE_TRY(hipEventCreate(&ev));
   }
   e->profiling = enable != 0;
@@ -1830,64 +1838,79 @@ int le_set_state(le_ctx* c, const double* phi, const double* omega, const double
   return LE_OK;
 }
 
+// One launch of a stage's kernels for le_time_stage: the state is read, what is
+// written is scratch.  d_tmp: the runs' descriptors with the scratch field in
+// phi's place, for the joined kernel that writes phi.
+void launch_timed(const Class& k, int stage, const Run* d, const Run* d_tmp, const StepArgs* sa,
+                  hipStream_t st) {
+  const int n = (int)k.members.size();
+  switch (stage) {
+    case 0:
+      if (k.joined_adv())
+        enqueue_stage(k, 1, d, n, sa, st);
+      else if (k.inertial)
+        k.ops.row_c2r(d, n, k.ny, B_OM_S, B_TMP, B_PS_S, B_TMP, 2, k.row_variant, st);
+      else
+        k.ops.row_c2r(d, n, k.ny, B_PS_S, B_TMP, B_PS_S, B_TMP, 1, k.row_variant, st);
+      break;
+    case 3:
+      if (k.joined_mu())
+        enqueue_stage(k, 4, d_tmp, n, sa, st);
+      else
+        k.ops.row_c2r(d, n, k.ny, B_PHIN, B_TMP, B_PHIN, B_TMP, 1, k.row_variant, st);
+      break;
+    case 4:
+      enqueue_stage(k, 4, k.joined_mu() ? d_tmp : d, n, sa, st);
+      break;
+    case 5:
+      if (k.inertial)
+        k.column(COL_FLOW, d, n, k.nx, sa, B_OMH, B_GH, B_PHIH, B_FH, k.col_flow_variant, st);
+      else
+        k.column(COL_STOKES, d, n, k.nx, sa, B_GH, B_GH, B_PHIN, B_PHIN, k.col_flow_variant, st);
+      break;
+    default:
+      enqueue_stage(k, stage, d, n, sa, st);
+      break;
+  }
+}
+
 int time_stage_of(Engine* e, int32_t stage, int32_t reps, double* ms_per_launch) {
   if (!e || stage < 0 || stage >= LE_NSTAGES || reps < 1 || !ms_per_launch) return LE_EINVAL;
   if (e->profiling) return LE_ESTATE;
   for (const RunHost& r : e->runs) LE_RC(set_args_one(e, r, e->step));
   hipEvent_t a = nullptr, b = nullptr;
-  if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) {
-    if (a) (void)hipEventDestroy(a);
-    return LE_EDEVICE;
-  }
-  // each launch covers every class, as one stage of a step does
-  auto launch = [&]() {
-    hipStream_t st = e->stream;
-    for (const Class& k : e->classes) {
-      const Run* d = e->d_desc + k.first;
-      const int n = (int)k.members.size();
-      const StepArgs* sa = e->d_args + k.first;
-      switch (stage) {
-        case 0:  // inverse row transforms of the state spectra, into the real scratch
-          if (k.inertial)
-            k.ops.row_c2r(d, n, k.ny, B_OM_S, B_TMP, B_PS_S, B_TMP, 2, k.row_variant, st);
-          else
-            k.ops.row_c2r(d, n, k.ny, B_PS_S, B_TMP, B_PS_S, B_TMP, 1, k.row_variant, st);
-          break;
-        case 1:
-          k.ops.advect(d, n, k.ny, sa, k.inertial, k.advect(), k.row_fwd_variant, st);
-          break;
-        case 2:
-          k.column(COL_CH, d, n, k.nx, sa, B_PHIH, B_FH, B_PHIN, B_PHIN, k.col_ch_variant,
-                       st);
-          break;
-        case 3:  // into the real scratch
-          k.ops.row_c2r(d, n, k.ny, B_PHIN, B_TMP, B_PHIN, B_TMP, 1, k.row_variant, st);
-          break;
-        case 4:
-          k.ops.mu_source(d, n, k.ny, sa, k.mu_variant, k.row_fwd_variant, st);
-          break;
-        default:  // outputs into the spectral scratch, the state untouched
-          if (k.inertial)
-            k.column(COL_FLOW, d, n, k.nx, sa, B_OMH, B_GH, B_PHIH, B_FH,
-                         k.col_flow_variant, st);
-          else
-            k.column(COL_STOKES, d, n, k.nx, sa, B_GH, B_GH, B_PHIN, B_PHIN,
-                         k.col_flow_variant, st);
-          break;
-      }
-    }
-  };
+  Run* d_tmp = nullptr;
+  std::vector<Run> h((size_t)e->nruns);
+  const size_t bytes = sizeof(Run) * h.size();
   int rc = LE_OK;
-  launch();
-  float ms = 0.0f;
-  if (hipEventRecord(a, e->stream) != hipSuccess) rc = LE_EDEVICE;
-  for (int i = 0; i < reps && !rc; ++i) launch();
-  if (!rc && (hipEventRecord(b, e->stream) != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
-              hipGetLastError() != hipSuccess || hipEventElapsedTime(&ms, a, b) != hipSuccess))
+  if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess ||
+      hipMemcpy(h.data(), e->d_desc, bytes, hipMemcpyDeviceToHost) != hipSuccess)
     rc = LE_EDEVICE;
-  (void)hipEventDestroy(a);
-  (void)hipEventDestroy(b);
-  if (!rc) *ms_per_launch = (double)ms / reps;
+  for (Run& r : h) r.buf[B_PHI] = r.buf[B_TMP];
+  rc = rc ? rc : alloc((void**)&d_tmp, bytes);
+  if (!rc && hipMemcpy(d_tmp, h.data(), bytes, hipMemcpyHostToDevice) != hipSuccess)
+    rc = LE_EDEVICE;
+  double total = 0.0;
+  for (const Class& k : e->classes) {
+    auto launch = [&] {
+      launch_timed(k, stage, e->d_desc + k.first, d_tmp + k.first, e->d_args + k.first, e->stream);
+    };
+    float ms = 0.0f;
+    if (rc) break;
+    launch();
+    if (hipEventRecord(a, e->stream) != hipSuccess) rc = LE_EDEVICE;
+    for (int i = 0; i < reps && !rc; ++i) launch();
+    if (!rc && (hipEventRecord(b, e->stream) != hipSuccess ||
+                hipEventSynchronize(b) != hipSuccess || hipGetLastError() != hipSuccess ||
+                hipEventElapsedTime(&ms, a, b) != hipSuccess))
+      rc = LE_EDEVICE;
+    const bool joined = !runs_in(k, {stage, false});
+    total += joined ? 0.5 * ms : ms;
+  }
+  if (a) (void)hipEventDestroy(a);
+  if (b) (void)hipEventDestroy(b);
+  if (d_tmp) (void)hipFree(d_tmp);
+  if (!rc) *ms_per_launch = total / reps;
   return rc;
 }
 
@@ -1972,6 +1995,12 @@ int le_checkpoint_load(le_ctx* c, const void* buf, int64_t bytes) {
 
 int le_time_stage(le_ctx* c, int32_t stage, int32_t reps, double* ms_per_launch) {
   return time_stage_of(c, stage, reps, ms_per_launch);
+}
+
+int le_joined(le_ctx* c) {
+  if (!c) return LE_EINVAL;
+  const Class& k = c->classes[c->runs[0].cls];
+  return (k.joined_adv() ? 1 : 0) | (k.joined_mu() ? 2 : 0);
 }
 
 int le_profile(le_ctx* c, int enable) { return profile_engine(c, enable); }

@@ -23,7 +23,7 @@ SYMBOLS = ("le_create", "le_step", "le_corrector_projection", "le_step_noalloc",
            "le_set_state", "le_strerror", "le_profile", "le_stage_times", "le_last_error",
            "le_batch_create", "le_batch_step", "le_batch_observables", "le_batch_get_state",
            "le_batch_profile", "le_batch_stage_times", "le_batch_destroy",
-           "le_tuning", "le_batch_tuning", "le_time_stage",
+           "le_tuning", "le_batch_tuning", "le_time_stage", "le_joined",
            "le_corrector_load", "le_step_corrected", "le_restrict", "le_set_fields",
            "le_corrector_audit", "le_corrector_status", "le_set_scheme", "le_set_recovery",
            "le_batch_set_scheme",
@@ -150,6 +150,8 @@ def lib():
         L.le_batch_stage_times.restype = C.c_int
         L.le_time_stage.argtypes = [C.c_void_p, C.c_int32, C.c_int32, _DP]
         L.le_time_stage.restype = C.c_int
+        L.le_joined.argtypes = [C.c_void_p]
+        L.le_joined.restype = C.c_int
         for f in (L.le_tuning, L.le_batch_tuning):
             f.argtypes = [C.c_void_p, C.POINTER(C.c_int32), C.c_int32]
             f.restype = C.c_int
@@ -339,7 +341,7 @@ class Context:
             raise LeError(rc, "le_profile")
 
     def stage_times(self):
-        """Dict stage -> (accumulated ms, launches)."""
+        """Dict stage -> (accumulated ms, steps); joined stages share their kernel's time."""
         self._check()
         ms = np.zeros(LE_NSTAGES)
         n = (C.c_int64 * LE_NSTAGES)()
@@ -350,13 +352,21 @@ class Context:
 
     def time_stage(self, stage: str, reps: int = 100) -> float:
         """Average microseconds of one launch of `stage` (back-to-back launches;
-        the state is not advanced)."""
+        the state is not advanced); half of its kernel's for a joined stage."""
         self._check()
         ms = C.c_double()
         rc = lib().le_time_stage(self._h, STAGES.index(stage), reps, C.byref(ms))
         if rc != LE_OK:
             raise LeError(rc, "le_time_stage")
         return ms.value * 1e3
+
+    def joined(self):
+        """Pairs of stages that one kernel of this run's step does."""
+        self._check()
+        bits = lib().le_joined(self._h)
+        if bits < 0:
+            raise LeError(bits, "le_joined")
+        return [STAGES[k:k + 2] for bit, k in ((1, 0), (2, 3)) if bits & bit]
 
     def tuning(self):
         """Kernel variants the autotuner chose for this run (list of one dict)."""
