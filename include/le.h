@@ -302,8 +302,8 @@ int le_joined(le_ctx* c);
  * inertia, runs in the group) for the life of the process, so later
  * contexts and batches of the same shape take the same kernels (and give the
  * same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
- * that text file across processes, LE_TUNE_CACHE=off times every creation
- * afresh.  Choices fixed through LE_TUNE_* are not cached.
+ * that text file across processes (lines of a library with other kernel shapes
+ * are passed over), LE_TUNE_CACHE=off times every creation afresh.  Choices fixed through LE_TUNE_* are not cached.
  * advect and mu_source are those of the stages' own kernels, which a step runs
  * where le_joined does not join the stage to the one before: on rows too long for
  * the joined kernels, for the upwind advection, and where LE_TUNE_ADV, _MU, _ROW

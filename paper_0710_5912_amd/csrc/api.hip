@@ -841,6 +841,11 @@ int pick(Engine* e, hipEvent_t a, hipEvent_t b, const int (&cand)[N], const char
 // LE_TUNE_CACHE=<file> also kept on disk across processes (one line per
 // entry: the key's six integers, then the six variants).  LE_TUNE_CACHE=off
 // re-times every context.  Variants fixed by LE_TUNE_* still apply.
+// The key's first integer holds the device and kShapes, which is raised whenever
+// a variant's number comes to mean another shape: entries of a file written with
+// other shapes are never found (1: column shapes of 8 and 16 values, several
+// columns per block; four-row advection only).
+constexpr int kShapes = 2;
 struct TuneEntry {
   int key[6];
   int val[6];  // advect, mu_source, column_ch, column_flow, row, row_fwd
@@ -859,7 +864,8 @@ bool tune_cache_off() {
 }
 
 void tune_key(const Class& k, int dev, int* key) {
-  const int v[6] = {dev, k.nx, k.ny, k.prec, k.inertial ? 1 : 0, (int)k.members.size()};
+  const int v[6] = {kShapes << 16 | dev, k.nx,  k.ny,
+                    k.prec,              k.inertial ? 1 : 0, (int)k.members.size()};
   std::memcpy(key, v, sizeof(v));
 }
 

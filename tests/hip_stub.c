@@ -13,12 +13,13 @@ static __thread int last;
 static pthread_mutex_t mu = PTHREAD_MUTEX_INITIALIZER;
 static struct { void* p; size_t n; int dev; } slot[SLOTS];
 static size_t used[DEVICES], limit_bytes = (size_t)1 << 62;
-static long mallocs, events;
+static long mallocs, events, launches;
 static int fail(int e) { return e ? (last = e) : 0; }
 
 size_t stub_used(int dev) { return used[dev]; }
 long stub_mallocs(void) { return mallocs; }
 long stub_events(void) { return events; }
+long stub_launches(void) { return launches; }
 void stub_limit(size_t n) { limit_bytes = n; }
 
 int hipGetDeviceCount(int* n) { *n = DEVICES; return OK; }
@@ -85,5 +86,6 @@ int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 1
 int hipLaunchKernel(const void* f, unsigned long long a, unsigned b, unsigned long long c, unsigned d,
                     void** args, size_t n, void* s) {
   (void)f; (void)a; (void)b; (void)c; (void)d; (void)args; (void)n; (void)s;
+  ++launches;
   return OK;
 }

@@ -19,7 +19,7 @@ HEAD = """
 import ctypes as C, sys
 stub = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
 stub.stub_used.restype = C.c_size_t
-stub.stub_mallocs.restype = stub.stub_events.restype = C.c_long
+stub.stub_mallocs.restype = stub.stub_events.restype = stub.stub_launches.restype = C.c_long
 stub.stub_limit.argtypes = [C.c_size_t]
 lib = C.CDLL(sys.argv[2])
 used = lambda: [stub.stub_used(d) for d in range(2)]
@@ -31,6 +31,18 @@ def grad(p, batch, h, w):
     x = (C.c_float * (2 * h * w * batch))()
     loss = C.c_double()
     return lib.le_cnn_grad(p, x, x, batch, C.byref(loss), None, None)
+def context(nx, ny):
+    sys.path.insert(0, ".")
+    from paper_0710_5912_amd import le
+    p = le.make_params(dict(nx=nx, ny=ny, lx=float(nx), ly=float(ny), gdot=0.01, A=1.0, B=1.0,
+                            kappa=1.0, M=1.0, eta=1.0, rho=1.0, dt=0.005))
+    c = C.c_void_p()
+    assert lib.le_create(C.byref(p), (C.c_double * (nx * ny))(), None, C.byref(c)) == 0
+    return c
+def tuning(c):
+    t = (C.c_int32 * 10)()
+    assert lib.le_tuning(c, t, 10) == 1
+    return list(t)
 """
 
 
@@ -99,14 +111,10 @@ def test_large_fields_are_read_back_from_any_threads_device(stub):
     call waits on belongs to the context's device."""
     child(stub, """
 import threading
-sys.path.insert(0, ".")
-from paper_0710_5912_amd import le
-p = le.make_params(dict(nx=1024, ny=512, lx=1024.0, ly=512.0, gdot=0.01, A=1.0, B=1.0, kappa=1.0,
-                        M=1.0, eta=1.0, rho=1.0, dt=0.005))
 phi = (C.c_double * (1024 * 512))()
-c, rc = C.c_void_p(), []
+rc = []
 stub.hipSetDevice(1)
-assert lib.le_create(C.byref(p), phi, None, C.byref(c)) == 0
+c = context(1024, 512)
 read = lambda: rc.append(lib.le_get_state(c, phi, phi, phi, None, None))   # a new thread: device 0
 t = threading.Thread(target=read)
 t.start()
@@ -114,3 +122,18 @@ t.join()
 assert rc == [0], rc
 lib.le_destroy(c)
 """)
+
+
+def test_tuning_file_of_other_shapes_is_passed_over(stub, tmp_path):
+    """A line as a library with other column shapes wrote it (device, grid, precision,
+    inertia, runs; six variants) leaves the choice alone; a written one is found."""
+    f = tmp_path / "tune"
+    f.write_text("0 64 64 0 1 1 33 33 4 4 5 5\n")
+    for _ in range(2):
+        child(stub, f"""
+import os
+os.environ["LE_TUNE_CACHE"] = {str(f)!r}
+assert tuning(context(64, 64))[4:] == [0, 0, 0, 0, 0, 0]
+""")
+    lines = [list(map(int, line.split())) for line in f.read_text().splitlines()]
+    assert len(lines) == 2 and lines[1][1:] == [64, 64, 0, 1, 1, 0, 0, 0, 0, 0, 0]
