@@ -304,8 +304,8 @@ int le_joined(le_ctx* c);
  * same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
  * that text file across processes (lines of a library with other kernel shapes
  * are passed over), LE_TUNE_CACHE=off times every creation afresh.  Choices fixed through LE_TUNE_* are not cached.
- * advect and mu_source are those of the stages' own kernels, which a step runs
- * where le_joined does not join the stage to the one before: on rows too long for
+ * advect and mu_source (0 where joined) are those of the stages' own kernels, which
+ * a step runs where le_joined does not join the stage to the one before: on rows too long for
  * the joined kernels, for the upwind advection, and where LE_TUNE_ADV, _MU, _ROW
  * or _ROW_FWD fixes a variant.  row also serves le_get_state and corrected steps,
  * row_fwd the observables, corrected steps and the upwind advection.

@@ -841,8 +841,9 @@ int pick(Engine* e, hipEvent_t a, hipEvent_t b, const int (&cand)[N], const char
 // LE_TUNE_CACHE=<file> also kept on disk across processes (one line per
 // entry: the key's six integers, then the six variants).  LE_TUNE_CACHE=off
 // re-times every context.  Variants fixed by LE_TUNE_* still apply.
-// The key's first integer holds the device and kShapes, which is raised whenever
-// a variant's number comes to mean another shape: entries of a file written with
+// The key's first integer holds the device, which stages are joined (their own
+// kernels are then not timed) and kShapes, which is raised whenever a variant's
+// number comes to mean another shape: entries of a file written with
 // other shapes are never found (1: column shapes of 8 and 16 values, several
 // columns per block; four-row advection only).
 constexpr int kShapes = 2;
@@ -864,8 +865,9 @@ bool tune_cache_off() {
 }
 
 void tune_key(const Class& k, int dev, int* key) {
-  const int v[6] = {kShapes << 16 | dev, k.nx,  k.ny,
-                    k.prec,              k.inertial ? 1 : 0, (int)k.members.size()};
+  const int joined = (k.fuse_adv ? 1 : 0) | (k.fuse_mu ? 2 : 0);
+  const int v[6] = {joined << 24 | kShapes << 16 | dev, k.nx, k.ny, k.prec, k.inertial ? 1 : 0,
+                    (int)k.members.size()};
   std::memcpy(key, v, sizeof(v));
 }
 
@@ -992,12 +994,15 @@ int autotune(Engine* e) {
       const int bins[3] = {B_TMP, B_R1, B_R2}, bouts[3] = {B_PHIH, B_FH, B_PHIN};
       k.ops.row_r2c_n(d, n, k.ny, bins, bouts, 3, v, st);
     });
-    rc = rc ? rc : pick(e, a, b, kAdvCand, "LE_TUNE_ADV", &k.adv_variant, [&](int v) {
-      k.ops.advect(d, n, k.ny, sa, k.inertial, v, k.row_fwd_variant, st);
-    });
-    rc = rc ? rc : pick(e, a, b, kMuCand, "LE_TUNE_MU", &k.mu_variant, [&](int v) {
-      k.ops.mu_source(d, n, k.ny, sa, v, k.row_fwd_variant, st);
-    });
+    // (joined stages run no kernel of these two)
+    if (!k.fuse_adv)
+      rc = rc ? rc : pick(e, a, b, kAdvCand, "LE_TUNE_ADV", &k.adv_variant, [&](int v) {
+        k.ops.advect(d, n, k.ny, sa, k.inertial, v, k.row_fwd_variant, st);
+      });
+    if (!k.fuse_mu)
+      rc = rc ? rc : pick(e, a, b, kMuCand, "LE_TUNE_MU", &k.mu_variant, [&](int v) {
+        k.ops.mu_source(d, n, k.ny, sa, v, k.row_fwd_variant, st);
+      });
     rc = rc ? rc : pick(e, a, b, kColCand, "LE_TUNE_COL_CH", &k.col_ch_variant, [&](int v) {
       k.column(COL_CH, d, n, k.nx, sa, B_PHIH, B_FH, B_PHIN, B_PHIN, v, st);
     });
@@ -1175,9 +1180,9 @@ int create_engine(int32_t n, const le_params* ps, const double* const* phi0s,
     }
     if (!rc) rc = solve_psi(e, r);
   }
-  if (!rc) rc = autotune(e);
   if (!variants_forced())
     for (Class& k : e->classes) fuse_shapes(&k);
+  if (!rc) rc = autotune(e);
   if (!rc && e->classes.size() > 1 && !(std::getenv("LE_CLASS_STREAMS") &&
                                         std::getenv("LE_CLASS_STREAMS")[0] == '0')) {
     if (hipEventCreateWithFlags(&e->fork_ev, hipEventDisableTiming) != hipSuccess)

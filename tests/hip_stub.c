@@ -83,9 +83,19 @@ int hipEventDestroy(void* e) { free(e); return OK; }
 int hipEventRecord(void* e, void* s) { return dev_of(e) == dev_of(s) ? OK : fail(HANDLE); }
 int hipEventSynchronize(void* e) { (void)e; return OK; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 1.0f; return OK; }
-int hipLaunchKernel(const void* f, unsigned long long a, unsigned b, unsigned long long c, unsigned d,
-                    void** args, size_t n, void* s) {
-  (void)f; (void)a; (void)b; (void)c; (void)d; (void)args; (void)n; (void)s;
+typedef struct { unsigned x, y, z; } dim3;
+int __hipPushCallConfiguration(dim3 g, dim3 b, size_t n, void* s) {
+  (void)g; (void)b; (void)n; (void)s;
+  return OK;
+}
+int __hipPopCallConfiguration(dim3* g, dim3* b, size_t* n, void** s) {
+  g->x = g->y = g->z = b->x = b->y = b->z = 1;
+  *n = 0;
+  *s = NULL;
+  return OK;
+}
+int hipLaunchKernel(const void* f, dim3 g, dim3 b, void** args, size_t n, void* s) {
+  (void)f; (void)g; (void)b; (void)args; (void)n; (void)s;
   ++launches;
   return OK;
 }

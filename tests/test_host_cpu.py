@@ -137,3 +137,19 @@ assert tuning(context(64, 64))[4:] == [0, 0, 0, 0, 0, 0]
 """)
     lines = [list(map(int, line.split())) for line in f.read_text().splitlines()]
     assert len(lines) == 2 and lines[1][1:] == [64, 64, 0, 1, 1, 0, 0, 0, 0, 0, 0]
+
+
+def test_only_stages_that_a_step_runs_are_timed(stub):
+    """6 + 6 row, 5 + 5 column candidates, each launched 1 + 9 times, the inverse rows
+    two kernels at a time; where the stages are apart also 21 + 18 stencil ones."""
+    child(stub, """
+import os
+launched = lambda: (context(64, 64), stub.stub_launches())[1]
+setup = 50
+joined = launched()
+assert joined <= 10 * (12 + 6 + 5 + 5) + setup, joined
+assert launched() <= joined + setup            # found in the cache
+at = stub.stub_launches()
+os.environ["LE_TUNE_ROW"] = "0"                # apart: an entry of its own
+assert launched() - at >= 10 * (6 + 5 + 5 + 21 + 18)
+""")
