@@ -911,22 +911,29 @@ void tune_cache_add(const int* key, const int* val) {
 }
 
 // The form a step's row stages take: the four-pass kernels (fused.hpp) on the
-// grids below, the separate stages elsewhere, under stage timing, for the upwind
-// scheme, and where LE_TUNE_* fixes a variant of theirs.  Measured (us per step,
-// inertial, FP64 / FP32, separate -> four-pass): 64^2 24.0 -> 16.0 / 22.4 ->
-// 14.9, 256^2 26.5 -> 21.2 / 24.3 -> 18.9, 512^2 39.3 -> 30.6 / 32.2 -> 26.2,
-// 1024 x 512 55.8 -> 43.5 / 54.3 -> 33.2, 1024^2 72.1 -> 57.2 / 54.7 -> 49.6,
-// 2048 x 1024 121 -> 105 / 90 -> 72.
+// grids below, the separate stages elsewhere, for the upwind scheme (its
+// advection), and where LE_TUNE_* fixes a variant of theirs.  By the grid alone,
+// not the number of runs, so that a run of a batch equals the run by itself bit
+// for bit.  Measured (us per step, inertial, FP64 / FP32, separate -> four-pass):
+// 64^2 23.8 -> 15.9 / 22.7 -> 14.8, 256^2 26.5 -> 20.8 / 24.1 -> 18.7,
+// 512^2 38.9 -> 33.0 / 31.9 -> 26.3, 1024 x 512 57.4 -> 44.4 / 54.0 -> 33.4,
+// 1024^2 73.0 -> 58.8 / 54.3 -> 49.3, 2048 x 1024 123.8 -> 105.8 / 91.4 -> 75.4.
 //  * 4 values per thread up to 256-point rows (nx <= 512) while the grid leaves
-//    SIMDs idle: half the serial chain of 8 (256^2 22.3 -> 21.2; 512 x 2048 FP64
-//    66.4 against 73.5 the other way);
+//    SIMDs idle: half the serial chain of 8 (256^2 22.5 -> 20.8; 512 x 2048 FP64
+//    68.0 against 73.8 the other way);
 //  * four rows per block re-transform fewer halo rows but need 256 blocks to
-//    fill the chip (1024^2 57.2 against 61.5 with two, 1024 x 512 50.0 against
-//    43.5);
+//    fill the chip (1024^2 58.8 against 63.4 with two, 1024 x 512 50.8 against
+//    44.4);
 //  * 16 KB rows (nx = 2048 FP64) leave one block per CU: worth it only where the
-//    separate mu stage has no strip form, nx > ny (2048 x 1024 121 -> 105,
-//    2048^2 197 -> 200), the advection from 512 rows on (2048 x 256 59.1 ->
-//    59.7); longer rows do not fit.
+//    separate mu stage has no strip form, nx > ny (2048 x 1024 123.8 -> 105.8,
+//    2048^2 201.9 -> 204.1), the advection from 512 rows on (2048 x 256 53.1 ->
+//    54.9); longer rows do not fit.  Its four-row mu spills 12 bytes per lane and
+//    is the faster shape all the same (two rows 114.5);
+//  * FP32 nx = 2048 with inertia: four-row advection spills 228 bytes per lane
+//    (2048 x 1024 78.7, two rows 75.4), and from ny = nx on its own kernel does
+//    better than either (2048^2 127.5 against 143.4 and 139.0, 2048 x 4096 263
+//    against 306 and 258); without inertia it does not spill (2048^2 98.7, two
+//    rows 100.4, apart 100.0).
 void fuse_shapes(Class* k) {
   const int nx = k->nx, ny = k->ny;
   const bool f64 = k->prec == LE_FP64;
@@ -935,6 +942,7 @@ void fuse_shapes(Class* k) {
     a = m = FUSE_2N;
   } else if (nx <= 1024 || (nx == 2048 && !f64)) {
     a = m = nx >= 1024 && ny >= 1024 ? FUSE_4W : FUSE_2W;
+    if (nx == 2048 && ny >= 1024 && k->inertial) a = ny < nx ? FUSE_2W : FUSE_NONE;
   } else if (nx == 2048 && ny < nx) {
     if (ny >= 512) a = FUSE_2W;
     m = ny >= 1024 ? FUSE_4W : FUSE_2W;

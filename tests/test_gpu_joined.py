@@ -40,7 +40,7 @@ def same(a, b):
 
 @pytest.mark.parametrize("nx,ny,precision,expect", [
     (8, 8, "fp64", [FLOW, MU]), (1024, 128, "fp64", [FLOW, MU]), (2048, 128, "fp64", [MU]),
-    (2048, 512, "fp64", [FLOW, MU]), (2048, 2048, "fp64", []), (2048, 2048, "fp32", [FLOW, MU]),
+    (2048, 512, "fp64", [FLOW, MU]), (2048, 2048, "fp64", []), (2048, 2048, "fp32", [MU]),
     (4096, 16, "fp64", [])])
 def test_joined_stages(nx, ny, precision, expect, monkeypatch):
     with make(nx, ny, precision, 1.0, gdot=0.0) as c:
