@@ -38,7 +38,6 @@ constexpr int pad32(int k) { return (k + 31) / 32 * 32; }
 __device__ __forceinline__ uint16_t f2bf(float f) {
   return __builtin_bit_cast(uint16_t, (__bf16)f);
 }
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(((unsigned)h) << 16); }
 
 // c += a b for one 32x32x16 tile.  Lane l holds A[l % 32][8 (l / 32) + e],
 // B[8 (l / 32) + e][l % 32] (e < 8) and C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
@@ -58,12 +57,6 @@ __device__ __forceinline__ float silu(float z) { return z * sigmoid(z); }
 __device__ __forceinline__ float silu_grad(float z) {
   const float s = sigmoid(z);
   return s * (1.0f + z * (1.0f - s));
-}
-
-// Pixel p shifted by (dy, dx) on the periodic H x W grid (powers of two).
-__device__ __forceinline__ int nb(int p, int dy, int dx, int H, int W, int lgW) {
-  const int py = p >> lgW, px = p & (W - 1);
-  return (((py + dy) & (H - 1)) << lgW) | ((px + dx) & (W - 1));
 }
 
 // ---------------------------------------------------------------- tiles

@@ -28,7 +28,7 @@ namespace le {
 // parts) to the real row, row_c2r's arithmetic without its branch at m = 0
 // (X[0] and X[L] give it by the general formula), left in lds[0 .. L) as pairs
 // and in v.  w0: the table entry t.
-template <typename T, int L, int E, bool WAVE, typename TW>
+template <typename T, int L, int E, typename TW>
 __device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const TW& tw, c2<double> w0,
                                          int t) {
   constexpr int P = L / E;
@@ -42,10 +42,10 @@ __device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const TW& tw, c2<
     const c2<T> b = cmulc(d, c2<T>{static_cast<T>(wd.x), static_cast<T>(wd.y)});
     v[q] = {a.x - b.y, a.y + b.x};
   }
-  group_sync<WAVE>();
-  fft_regs<T, L, E, +1, WAVE>(v, lds, 1, tw, t);
+  group_sync<true>();
+  fft_regs<T, L, E, +1, true>(v, lds, 1, tw, t);
   const T sc = static_cast<T>(1.0 / (2.0 * L));
-  group_sync<WAVE>();
+  group_sync<true>();
 #pragma unroll
   for (int q = 0; q < E; ++q) {
     v[q] = {v[q].x * sc, v[q].y * sc};
@@ -56,25 +56,26 @@ __device__ __forceinline__ void rows_c2r(c2<T>* v, c2<T>* lds, const TW& tw, c2<
 // Real row pairs v[q] = pair t + q P to the complex transform z of the packed
 // row in lds[0 .. L), and z[0] again in lds[L] (rows_out reads the mirror of
 // m = 0 there).
-template <typename T, int L, int E, bool WAVE, typename TW>
+template <typename T, int L, int E, typename TW>
 __device__ __forceinline__ void rows_r2c_z(c2<T>* v, c2<T>* lds, const TW& tw, int t) {
   constexpr int P = L / E;
-  fft_regs<T, L, E, -1, WAVE>(v, lds, 1, tw, t);
-  group_sync<WAVE>();
+  fft_regs<T, L, E, -1, true>(v, lds, 1, tw, t);
+  group_sync<true>();
 #pragma unroll
   for (int q = 0; q < E; ++q) lds[t + q * P] = v[q];
   if (t == 0) lds[L] = v[0];
 }
 
-// Shapes.  E values per thread, P = L/E threads per transform (up to a
-// wavefront its passes need no block barrier).  LS: row stride in LDS, L + 1
+// Shapes.  E values per thread, P = L/E threads per transform, within one
+// wavefront (its passes need no block barrier, and groups beyond the rows sit
+// them out).  LS: row stride in LDS, L + 1
 // modes, two mod 8 (FP64) and mod 16 (FP32), so the tile runs of consecutive
 // rows fall on distinct banks.
 template <typename T, int L_, int NR_, int NF_, int E_>
 struct FuseCfg {
   static constexpr int L = L_, NR = NR_, NF = NF_, E = E_;
   static constexpr int P = L / E;
-  static constexpr bool WAVE = P <= 64;
+  static_assert(P <= 64, "a transform lies within one wavefront");
   static constexpr int LS = L + 2;
   // advection: inverse rows, forward rows, transform groups
   static constexpr int AI = (NF == 3 ? 2 : 1) * (NR + 2), AO = NF * NR;
@@ -275,9 +276,9 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB),
     put_phi(second);
   __syncthreads();
   ptw.form();
-  if (!C::WAVE || grp < C::AI) {  // (a group of several waves holds block barriers)
+  if (grp < C::AI) {
     c2<T> v[E];
-    rows_c2r<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, w0, t);
+    rows_c2r<T, L, E>(v, rows + grp * LS, ptw, w0, t);
   }
   __syncthreads();
   by_diag(geo.r, st.off, [&](auto diag) {
@@ -351,12 +352,12 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, NF, E_>::ATPB),
   });
   __syncthreads();
   // forward transforms, group f NR + r: phi_h, f, omega_h
-  if (!C::WAVE || grp < C::AO) {
+  if (grp < C::AO) {
     c2<T> v[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) v[q] = rows[grp * LS + t + q * P];
-    group_sync<C::WAVE>();
-    rows_r2c_z<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, t);
+    group_sync<true>();
+    rows_r2c_z<T, L, E>(v, rows + grp * LS, ptw, t);
   }
   __syncthreads();
   if constexpr (NF == 3) {
@@ -401,9 +402,9 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, 2, E_>::MTPB)) void k_phi_m
   in.put(rows, LS);
   __syncthreads();
   ptw.form();
-  if (!C::WAVE || grp < C::MI) {
+  if (grp < C::MI) {
     c2<T> v[E];
-    rows_c2r<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, w0, t);
+    rows_c2r<T, L, E>(v, rows + grp * LS, ptw, w0, t);
     if (grp >= 2 && grp < NR + 2) {
       auto phi = reinterpret_cast<gp<c2<T>>>(bufp<T>(R, B_PHI)) + (size_t)(j0 - 2 + grp) * L;
 #pragma unroll
@@ -476,12 +477,12 @@ __global__ __launch_bounds__((FuseCfg<T, NX / 2, NR, 2, E_>::MTPB)) void k_phi_m
     }
   });
   __syncthreads();
-  if (!C::WAVE || grp < NR) {
+  if (grp < NR) {
     c2<T> v[E];
 #pragma unroll
     for (int q = 0; q < E; ++q) v[q] = rows[grp * LS + t + q * P];
-    group_sync<C::WAVE>();
-    rows_r2c_z<T, L, E, C::WAVE>(v, rows + grp * LS, ptw, t);
+    group_sync<true>();
+    rows_r2c_z<T, L, E>(v, rows + grp * LS, ptw, t);
   }
   __syncthreads();
   gp<c2<T>> const X[1] = {bufp<c2<T>>(R, B_GH)};
