@@ -290,25 +290,26 @@ int le_joined(le_ctx* c);
  * stencil and the row transforms in one kernel (other nx: as k);
  * column_*: block shape 0 .. 4 (4, 8 or 16 values per thread; the pass's two
  * fields one after the other or side by side); row / row_fwd: shape 0 .. 5 of
- * the inverse / forward row transforms (8 or 4 values per thread; all or a quarter of the rows per
- * block, or 4 and 5: groups of four consecutive rows stored or loaded
- * together)), at most cap
- * values in all, and returns the number of
- * groups (LE_EINVAL for NULL c, cap < 0 or out NULL with cap > 0).  The
+ * the inverse / forward row transforms (8 or 4 values per thread; all or a
+ * quarter of the rows per block, or 4 and 5: groups of four consecutive rows
+ * stored or loaded together)), at most cap values in all, and returns the number
+ * of groups (LE_EINVAL for NULL c, cap < 0 or out NULL with cap > 0).  The
  * environment variables LE_TUNE_ADV, LE_TUNE_MU, LE_TUNE_COL_CH,
  * LE_TUNE_COL_FLOW, LE_TUNE_ROW and LE_TUNE_ROW_FWD, when set, fix the
  * corresponding variant at creation (LE_TUNE_LOG=1 prints every candidate's
  * time to stderr).  The choices are cached per (device, nx, ny, precision,
- * inertia, runs in the group) for the life of the process, so later
- * contexts and batches of the same shape take the same kernels (and give the
- * same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
+ * inertia, runs in the group, joined stages) for the life of the process, so
+ * later contexts and batches of the same shape take the same kernels (and give
+ * the same results) without re-timing; LE_TUNE_CACHE=<file> also keeps them in
  * that text file across processes (lines of a library with other kernel shapes
- * are passed over), LE_TUNE_CACHE=off times every creation afresh.  Choices fixed through LE_TUNE_* are not cached.
- * advect and mu_source (0 where joined) are those of the stages' own kernels, which
- * a step runs where le_joined does not join the stage to the one before: on rows too long for
- * the joined kernels, for the upwind advection, and where LE_TUNE_ADV, _MU, _ROW
- * or _ROW_FWD fixes a variant.  row also serves le_get_state and corrected steps,
- * row_fwd the observables, corrected steps and the upwind advection.
+ * are passed over), LE_TUNE_CACHE=off times every creation afresh.  Choices
+ * fixed through LE_TUNE_* are not cached.
+ * advect and mu_source (0 where joined) are those of the stages' own kernels,
+ * which a step runs where le_joined does not join the stage to the one before:
+ * on rows too long for the joined kernels, for the upwind advection, and where
+ * LE_TUNE_ADV, _MU, _ROW or _ROW_FWD fixes a variant.  row also serves
+ * le_get_state and corrected steps, row_fwd the observables, corrected steps and
+ * the upwind advection.
  */
 enum { LE_TUNING_FIELDS = 10 };
 int le_tuning(le_ctx* c, int32_t* out, int32_t cap);

@@ -22,7 +22,7 @@ constexpr int kOffW[kCnnLayers] = {0, 608, 9856, 19104};
 constexpr int kOffB[kCnnLayers] = {576, 9824, 19072, 19680};
 
 // A training step takes as many samples at once as hold kGroupPixels pixels
-// (850 B each; 16 of 256^2: 733 us per step, in groups of 8 765, of 4 862).
+// (850 to 1010 B each; 16 of 256^2: 655 us per step, in groups of 8 705, of 4 830).
 // Blocks over the tiles of a batch: three per CU, as many as are resident, of
 // the 32-channel forward (1024 blocks: 66 -> 64 us, last layer 38 -> 32), four
 // of the others; of the weight gradient as many as are resident, so that its

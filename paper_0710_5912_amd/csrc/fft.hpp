@@ -10,7 +10,10 @@
 //   * dft_reg        radix-R DFT on R values held in registers (R <= 16);
 //   * fft_group      length-L complex FFT done by a group of L/E threads that
 //                    each hold E values, exchanging through LDS between the
-//                    passes (Stockham autosort: natural order in and out);
+//                    passes (Stockham autosort: natural order in and out),
+//                    its twiddles read from the table pass by pass;
+//   * fft_regs       the same for kernels that run several transforms of one
+//                    length, the passes' twiddles read once (PassSet);
 //   * row_r2c/c2r    real row of 2L values <-> L packed complex values.
 //
 // Forward transforms are unnormalised, F[a](m) = sum_i a_i exp(-2 pi i m i/n).

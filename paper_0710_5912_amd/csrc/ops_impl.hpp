@@ -172,7 +172,8 @@ struct RowLaunch {
       default:
         // FP32 rows of 4096: eight rows to a batch where the strip holds them (same
         // LDS per CU as two blocks of four): whole 128-byte runs per store and
-        // 10 rows read for 8 instead of 6 for 4; 4096^2 210 -> 170 us
+        // 10 rows read for 8 instead of 6 for 4; 4096^2 191 -> 162 us, though the
+        // registers of 1024 threads (128) spill 96 bytes per lane
         if constexpr (sizeof(T) == 4 && L == 2048)
           if (!mu && *rows >= 8)
             return batch_shape<8, 16>(mu, runs, sa, ny, gb, *rows, inertial, st);
