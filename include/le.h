@@ -116,8 +116,7 @@ int le_step(le_ctx* c, int64_t nsteps);
 
 /*
  * le_step without a context, for callers that cannot allocate device memory
- * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * allocation).  phi_dev, omega_dev, psi_dev: the caller's device arrays of
+ * (tight serving loops, harnesses that forbid allocation).  phi_dev, omega_dev, psi_dev: the caller's device arrays of
  * nx*ny doubles, row-major [j][i] (x fastest), the real fields phi, omega,
  * psi of step step0 >= 0 (the state le_get_state returns; omega_dev is
  * ignored and may be NULL when rho == 0); on return they hold the state of
@@ -128,9 +127,9 @@ int le_step(le_ctx* c, int64_t nsteps);
  * ends; the call allocates nothing.  Limits: p->precision == LE_FP64 and a
  * grid whose buffers fit that array (up to 256 x 256, or equivalently small
  * non-square grids), else LE_EINVAL (le_last_error names the size).  The
- * kernel shapes are the defaults (no autotuning), so results equal a
+ * kernel shapes go by the grid alone (no autotuning), so results equal a
  * context's to rounding, not bit for bit.  Runs on p->stream (NULL: the null
- * stream) and returns after draining it.  No recovery: LE_ENONFINITE leaves
+ * stream) and returns after draining it (so not under stream capture).  No recovery: LE_ENONFINITE leaves
  * the non-finite state in the caller's arrays.  Calls on one device share
  * the static array: calls that overlap in time on one device race (run them
  * on one stream, one after another); the array keeps the last call's
